@@ -51,7 +51,8 @@ struct ChunkPtrs {
 // flight per lane, 64 VGPRs) stream as fast as one in the isolated pass and
 // make the overlapped 8192^3 schedule 1-2 % shorter (the own-term reduce
 // 6 % faster); four positions fall in between.  The default grid is one
-// workgroup per CU.
+// workgroup per CU.  At most 64 VGPRs (8 waves per SIMD): what the 256x256
+// GEMM's two waves leave of a SIMD's 512, so that both fit on one CU.
 //
 // OWN: the first term is a bf16 buffer (this GPU's own contribution, e.g. its
 // GEMM output), widened exactly to binary32; the NC (or nchunks) fp32 chunks
@@ -241,8 +242,11 @@ int clamp_wgs(size_t work_units, int wanted, int threads) {
 
 // Positions per lane per trip of the vector chunk sum for a number of terms
 // (fp32 chunks plus the own term); the launch table and the pacing period
-// both take it from here.
-constexpr int reduce_unroll(int terms) { return terms == 2 ? 4 : (terms == 4 || terms == 8) ? 2 : 1; }
+// both take it from here.  With 64-bit offsets two positions of 8 terms would
+// need more than the 64 VGPRs that fit beside the 256x256 GEMM's waves.
+constexpr int reduce_unroll(int terms, bool off32) {
+  return terms == 2 ? 4 : (terms == 4 || (terms == 8 && off32)) ? 2 : 1;
+}
 
 // Loads in flight per lane of the vector permutation (launch, pacing and the
 // 32-bit offset check).  With four-wave workgroups 2 and 8 gave no shorter
@@ -267,10 +271,10 @@ void launch_reduce(int nchunks, int g, hipStream_t s, const ChunkPtrs &cp, size_
                    const uint16_t *own, int prio, uint32_t pace, const KHooks &tr) {
   // instantiations by the number of terms (own + fp32 chunks)
   switch (nchunks + (OWN ? 1 : 0)) {
-    case 2: hipLaunchKernelGGL((reduce_vec_kernel<OWN ? 1 : 2, reduce_unroll(2), OFF32, OWN>), dim3(g), dim3(kReduceThreads), 0, s, cp, nchunks, nvec, out, own, prio, pace, tr); break;
-    case 4: hipLaunchKernelGGL((reduce_vec_kernel<OWN ? 3 : 4, reduce_unroll(4), OFF32, OWN>), dim3(g), dim3(kReduceThreads), 0, s, cp, nchunks, nvec, out, own, prio, pace, tr); break;
-    case 8: hipLaunchKernelGGL((reduce_vec_kernel<OWN ? 7 : 8, reduce_unroll(8), OFF32, OWN>), dim3(g), dim3(kReduceThreads), 0, s, cp, nchunks, nvec, out, own, prio, pace, tr); break;
-    case 16: hipLaunchKernelGGL((reduce_vec_kernel<OWN ? 15 : 16, reduce_unroll(16), OFF32, OWN>), dim3(g), dim3(kReduceThreads), 0, s, cp, nchunks, nvec, out, own, prio, pace, tr); break;
+    case 2: hipLaunchKernelGGL((reduce_vec_kernel<OWN ? 1 : 2, reduce_unroll(2, OFF32), OFF32, OWN>), dim3(g), dim3(kReduceThreads), 0, s, cp, nchunks, nvec, out, own, prio, pace, tr); break;
+    case 4: hipLaunchKernelGGL((reduce_vec_kernel<OWN ? 3 : 4, reduce_unroll(4, OFF32), OFF32, OWN>), dim3(g), dim3(kReduceThreads), 0, s, cp, nchunks, nvec, out, own, prio, pace, tr); break;
+    case 8: hipLaunchKernelGGL((reduce_vec_kernel<OWN ? 7 : 8, reduce_unroll(8, OFF32), OFF32, OWN>), dim3(g), dim3(kReduceThreads), 0, s, cp, nchunks, nvec, out, own, prio, pace, tr); break;
+    case 16: hipLaunchKernelGGL((reduce_vec_kernel<OWN ? 15 : 16, reduce_unroll(16, OFF32), OFF32, OWN>), dim3(g), dim3(kReduceThreads), 0, s, cp, nchunks, nvec, out, own, prio, pace, tr); break;
     default: hipLaunchKernelGGL((reduce_vec_kernel<0, 1, OFF32, OWN>), dim3(g), dim3(kReduceThreads), 0, s, cp, nchunks, nvec, out, own, prio, pace, tr); break;
   }
 }
@@ -302,15 +306,15 @@ int reduce_launch(const ReduceCall &c, hipStream_t s) {
       tr.ack_target = (nvec > 0 ? (uint32_t)clamp_wgs(nvec, wgs, kReduceThreads) : 0u) + (tail ? 1u : 0u);
     if (nvec > 0) {
       int g = clamp_wgs(nvec, wgs, kReduceThreads);
-      // positions per lane per trip of each instantiation, and the bytes
-      // one position moves
       const int terms = c.nchunks + (own ? 1 : 0);
-      const int unroll = reduce_unroll(terms);
-      const double pos_bytes = 16.0 * (c.nchunks + 1) + (own ? 8.0 : 0.0);
-      const uint32_t pace = pace_ticks((double)g * kReduceThreads * unroll * pos_bytes, c.rate_gbs);
       // 32-bit offsets when the largest byte offset the loop can form, (nvec
       // plus one unrolled grid stride) * 16, stays below 2^32
       const bool off32 = ((double)nvec + 4.0 * g * kReduceThreads) * 16.0 < 4294967296.0;
+      // positions per lane per trip of each instantiation, and the bytes
+      // one position moves
+      const int unroll = reduce_unroll(terms, off32);
+      const double pos_bytes = 16.0 * (c.nchunks + 1) + (own ? 8.0 : 0.0);
+      const uint32_t pace = pace_ticks((double)g * kReduceThreads * unroll * pos_bytes, c.rate_gbs);
       if (own) {
         if (off32) launch_reduce<true, true>(c.nchunks, g, s, cp, nvec, c.out, c.own, prio, pace, tr);
         else launch_reduce<false, true>(c.nchunks, g, s, cp, nvec, c.out, c.own, prio, pace, tr);

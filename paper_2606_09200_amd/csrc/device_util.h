@@ -91,10 +91,10 @@ __device__ __forceinline__ void dep_wait(const KHooks &t) {
 __device__ __forceinline__ HookStart hooks_begin(const KHooks &t) {
   if (t.wait != nullptr) dep_wait(t);
   HookStart s{0, 0};
-  if (threadIdx.x == 0 && (t.stamps != nullptr || t.wg != nullptr)) {
+  if (t.stamps != nullptr || t.wg != nullptr) {  // uniform: the stamps stay in scalar registers
     s.ticks = now_ticks();
     s.cycles = now_cycles();
-    if (t.stamps != nullptr)
+    if (threadIdx.x == 0 && t.stamps != nullptr)
       atomicMin(reinterpret_cast<unsigned long long *>(t.stamps), (unsigned long long)s.ticks);
   }
   return s;

@@ -11,12 +11,14 @@
 // reads) or N x K (occ_gemm_bt: C = A * B^T, a linear layer's weight layout,
 // both MFMA operands read from LDS as 16-byte rows).
 //
-// The kernels live in gemm_dl.h (direct-to-LDS tiles, both layouts),
+// The kernels live in gemm_pp.h (256x256 tiles, both layouts), gemm_dl.h
+// (smaller direct-to-LDS tiles, both layouts),
 // gemm_tiled.h (register-staged tiles, the paper's opt1/opt2 with B N x K),
 // gemm_skinny.h and gemm_skinny_ldsb.h (M <= 16, B N x K) and
 // gemm_skinny_kn.h (M <= 16, B K x N); this file holds the variant table, the
 // launch plan and the launcher.
 #include "gemm_dl.h"
+#include "gemm_pp.h"
 #include "gemm_skinny.h"
 #include "gemm_skinny_kn.h"
 #include "gemm_skinny_ldsb.h"
@@ -73,6 +75,13 @@ constexpr Variant make_dl_variant(int id, const char *name) {
                  dl_kmax<T>(), 0, T::BKN, dl_nmax<T>()};
 }
 
+// The two-group kernel addresses its operands in the same way.
+template <class T>
+constexpr Variant make_pp_variant(int id, const char *name) {
+  return Variant{id, T::BM, T::BN, T::BK, T::NT, T::LDS_BYTES, gemm_pp_kernel<T>, nullptr, name,
+                 dl_kmax<T>(), 0, T::BKN, dl_nmax<T>()};
+}
+
 template <int WAVES, int UNROLL>
 constexpr Variant make_skinny_variant(int id, const char *name) {
   return Variant{id, 16, 16, kSkinnyKB * UNROLL, 64 * WAVES, (WAVES - 1) * 64 * 16, nullptr,
@@ -104,14 +113,12 @@ using T64x64_opt2 = Tile<64, 64, 64, 2, 2, 1>;   // Table 1 opt2: 64x64x64
 // shapes (one k-step's DMA in flight while the previous one is used)
 using D64x64_4w_2s = Tile<64, 64, 64, 2, 2, 2>;
 using D128x128_4w_3s = Tile<128, 128, 64, 2, 2, 3>;
-using P256x256_8w_2s = Tile<256, 256, 64, 2, 4, 2, true>;
 // two workgroups per CU: each has its own barriers, so one computes while the
 // other waits (48 KiB of LDS, 4 waves of 128x64 each)
 using P128x256k32_4w_2s = Tile<128, 256, 32, 1, 4, 2, true, 2>;
 
 // B stored K x N (occ_gemm): the same tiles with the B tile staged as stored
 // and its MFMA operands read with LDS transpose reads
-using PKN256x256_8w_2s = Tile<256, 256, 64, 2, 4, 2, true, 1, true>;
 using KN128x128_4w_3s = Tile<128, 128, 64, 2, 2, 3, false, 1, true>;
 using KN64x64_opt1 = Tile<64, 64, 32, 2, 2, 1, false, 1, true>;   // Table 1 opt1, one stage
 using KN64x64_opt2 = Tile<64, 64, 64, 2, 2, 1, false, 1, true>;   // Table 1 opt2, one stage
@@ -124,12 +131,12 @@ const Variant kVariants[] = {
     make_variant<T64x64_opt2>(7, "64x64x64 opt2, B N x K"),
     make_dl_variant<D64x64_4w_2s>(9, "dl 64x64x64 4w 2st, B N x K"),
     make_dl_variant<D128x128_4w_3s>(14, "dl 128x128x64 4w 3st, B N x K"),
-    make_dl_variant<P256x256_8w_2s>(16, "dl+pipe 256x256x64 8w 2st, B N x K"),
+    make_pp_variant<PpTile<false>>(16, "pp 256x256x64 8w 2st, B N x K"),
     make_skinny_variant<8, 8>(21, "skinny M<=16, 8 waves, unroll 8, B N x K"),
     make_dl_variant<P128x256k32_4w_2s>(25, "dl+pipe 128x256x32 4w 2st 2wg/cu, B N x K"),
     make_skinny_ldsb_variant<8, 2, 32>(34, "skinny M<=16, B via LDS in 256-byte row pieces, A in registers, 8 waves, K<=8192, K%1024==0, B N x K"),
     // B stored K x N
-    make_dl_variant<PKN256x256_8w_2s>(32, "dl+pipe 256x256x64 8w 2st, B K x N"),
+    make_pp_variant<PpTile<true>>(32, "pp 256x256x64 8w 2st, B K x N"),
     make_skinny_kn_variant<4, 2, 128>(33, "skinny M<=16, 128-column units, 4 waves, 2 LDS stages, B K x N"),
     make_dl_variant<KN128x128_4w_3s>(35, "dl 128x128x64 4w 3st, B K x N"),
     make_dl_variant<KN64x64_opt1>(36, "dl 64x64x32 opt1 1st, B K x N"),

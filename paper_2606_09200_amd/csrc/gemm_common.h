@@ -16,6 +16,23 @@ __device__ __forceinline__ uint16_t to_bf16(float f) {
   return __builtin_bit_cast(uint16_t, static_cast<__bf16>(f));  // round to nearest even
 }
 
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
+  return (uint32_t)to_bf16(lo) | ((uint32_t)to_bf16(hi) << 16);
+}
+
+// 16-byte non-temporal stores of C (written once and not read again by the
+// kernel) at a byte offset (below 2^32, a multiple of 16) of `base`; offsets at
+// or past `bytes` store nothing.  base and bytes are wave-uniform.
+struct CStore {
+  __amdgpu_buffer_rsrc_t rsrc;
+  __device__ __forceinline__ CStore(uint16_t *base, uint32_t bytes)
+      : rsrc(__builtin_amdgcn_make_buffer_rsrc(base, 0, (int)bytes, 0x00020000)) {}
+  __device__ __forceinline__ void put(u32x4 v, uint32_t off) const {
+    constexpr int kNt = 2;  // cache policy bit: non-temporal
+    __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)off, 0, kNt);
+  }
+};
+
 // ---------------------------------------------------------------------------
 // Tiled kernel.  A workgroup owns a BM x BN output tile; WM x WN waves each
 // own a (BM/WM) x (BN/WN) sub-tile made of 32x32 MFMA blocks.  Each k-step of

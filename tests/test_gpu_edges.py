@@ -1,0 +1,41 @@
+"""Edges of the kernels' tiles, batches and dispatch rules (GPU, against the oracle).
+
+GEMM cases use small-integer operands, whose fp32 partial sums are exact in any
+order, so every comparison is bit for bit; so are the chunk sums and the
+permutation by their definition."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2606_09200_amd import binding as occ
+from gpu_common import DEV, bf16_bits
+
+pytestmark = pytest.mark.gpu
+
+
+def int_gemm(M, N, K, layout, variant=0, grid_cap=0, seed=0):
+    """(result bits, oracle bits) of an integer GEMM; C starts as NaN."""
+    g = torch.Generator().manual_seed(seed)
+    A = torch.randint(-2, 3, (M, K), generator=g).to(torch.bfloat16)
+    B = torch.randint(-2, 3, (K, N) if layout == "kn" else (N, K), generator=g).to(torch.bfloat16)
+    C = torch.full((M, N), float("nan"), device=DEV, dtype=torch.bfloat16)
+    f = occ.occ_gemm_ex if layout == "kn" else occ.occ_gemm_bt_ex
+    f(A.to(DEV), B.to(DEV), C, variant=variant, grid_cap=grid_cap)
+    torch.cuda.synchronize()
+    return bf16_bits(C), oracle.gemm_bf16(A, B, M, N, K, b_layout=layout)
+
+
+# 256x256 tile: one to five k-steps (the two-stage pipeline's fill and drain), a
+# last k-step of one 8-wide chunk, one row or column more or less than a tile,
+# and rows of C that are not 16-byte aligned (B N x K only)
+@pytest.mark.parametrize("layout", ["kn", "nk"])
+@pytest.mark.parametrize("M,N,K", [(256, 256, 8), (255, 248, 64), (257, 264, 72), (256, 512, 128), (1, 8, 136),
+                                   (511, 136, 192), (300, 520, 264), (129, 257, 320), (64, 131, 200)])
+def test_large_tile_edges(layout, M, N, K):
+    if layout == "kn":
+        N = (N + 7) // 8 * 8
+    variant = 32 if layout == "kn" else 16
+    for cap in (0, 1):  # one workgroup per tile, and one that walks all tiles
+        got, ref = int_gemm(M, N, K, layout, variant, cap, seed=M + K)
+        assert np.array_equal(got, ref), cap
