@@ -82,8 +82,11 @@ __global__ __launch_bounds__(kReduceThreads) void reduce_vec_kernel(ChunkPtrs cp
     __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(reinterpret_cast<char *>(out) + k * (I)sizeof(f32x4)));
   };
   auto ld_own = [&](I k) {
-    const u32x2 w = __builtin_nontemporal_load(
-        reinterpret_cast<const u32x2 *>(reinterpret_cast<const char *>(own) + k * (I)sizeof(u32x2)));
+    // device-scope: written by a GEMM that may still be running (KHooks)
+    const uint64_t d = __hip_atomic_load(
+        reinterpret_cast<const uint64_t *>(reinterpret_cast<const char *>(own) + k * (I)sizeof(uint64_t)),
+        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const u32x2 w = {(uint32_t)d, (uint32_t)(d >> 32)};
     f32x4 r;
     r[0] = widen_bf16(w[0] & 0xFFFFu);
     r[1] = widen_bf16(w[0] >> 16);
@@ -154,7 +157,9 @@ __global__ __launch_bounds__(kReduceThreads) void reduce_scalar_kernel(ChunkPtrs
   const HookStart t0 = hooks_begin(tr);
   const size_t stride = (size_t)gridDim.x * kReduceThreads;
   for (size_t j = first + (size_t)blockIdx.x * kReduceThreads + threadIdx.x; j < len; j += stride) {
-    float acc = own != nullptr ? widen_bf16(own[j]) : cp.p[0][j];
+    float acc = own != nullptr
+                    ? widen_bf16(__hip_atomic_load(own + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                    : cp.p[0][j];
     for (int c = own != nullptr ? 0 : 1; c < nchunks; ++c) acc = acc + cp.p[c][j];
     out[j] = acc;
   }

@@ -20,16 +20,26 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   return (uint32_t)to_bf16(lo) | ((uint32_t)to_bf16(hi) << 16);
 }
 
-// 16-byte non-temporal stores of C (written once and not read again by the
-// kernel) at a byte offset (below 2^32, a multiple of 16) of `base`; offsets at
-// or past `bytes` store nothing.  base and bytes are wave-uniform.
+// Stores of C, non-temporal (written once and not read again by the kernel).
+// `through`: at device scope, i.e. through the XCD's L2 to memory, so that a
+// store that has completed is visible to the whole device (the hooks'
+// release, see hooks_end).
+__device__ __forceinline__ void store_c(uint16_t *p, uint16_t v, bool through) {
+  if (through) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else __builtin_nontemporal_store(v, p);
+}
+
+// The same, 16 bytes at a byte offset (below 2^32, a multiple of 16) of `base`;
+// offsets at or past `bytes` store nothing.  base and bytes are wave-uniform.
 struct CStore {
   __amdgpu_buffer_rsrc_t rsrc;
-  __device__ __forceinline__ CStore(uint16_t *base, uint32_t bytes)
-      : rsrc(__builtin_amdgcn_make_buffer_rsrc(base, 0, (int)bytes, 0x00020000)) {}
+  bool through;
+  __device__ __forceinline__ CStore(uint16_t *base, uint32_t bytes, bool through_)
+      : rsrc(__builtin_amdgcn_make_buffer_rsrc(base, 0, (int)bytes, 0x00020000)), through(through_) {}
   __device__ __forceinline__ void put(u32x4 v, uint32_t off) const {
-    constexpr int kNt = 2;  // cache policy bit: non-temporal
-    __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)off, 0, kNt);
+    constexpr int kNt = 2, kDevice = 16;  // cache policy bits: non-temporal, device scope (sc1)
+    if (through) __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)off, 0, kNt | kDevice);
+    else __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)off, 0, kNt);
   }
 };
 

@@ -257,7 +257,7 @@ __global__ __launch_bounds__(T::NT, T::MINB) void gemm_dl_kernel(const uint16_t 
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             const int m = mb + 8 * (r >> 2) + (r & 3);
-            if (m < M) __builtin_nontemporal_store(to_bf16(acc[i][j][r]), &C[(size_t)m * N + n]);
+            if (m < M) store_c(&C[(size_t)m * N + n], to_bf16(acc[i][j][r]), tr.release);
           }
         }
         // keep the accumulator reads of one block next to its stores (the

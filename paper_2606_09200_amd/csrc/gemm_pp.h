@@ -238,7 +238,7 @@ __global__ __launch_bounds__(T::NT) void gemm_pp_kernel(const uint16_t *__restri
       for (int i = 0; i < 4; ++i) {
         const int mb = m0 + h * 128 + half * 64 + i * 16;  // first row of the block
         const uint32_t c_bytes = (uint32_t)min(16, max(0, M - mb)) * (uint32_t)N * 2u;
-        const CStore cs(C + (size_t)mb * N, c_bytes);
+        const CStore cs(C + (size_t)mb * N, c_bytes, tr.release);
 #pragma unroll
         for (int hb = 0; hb < 2; ++hb) {
           const f32x4 p = acc[h][i][2 * hb], q = acc[h][i][2 * hb + 1];
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(T::NT) void gemm_pp_kernel(const uint16_t *__restri
 #pragma unroll
             for (int e = 0; e < 8; ++e)
               if (n + e < N)
-                __builtin_nontemporal_store((uint16_t)(v[e >> 1] >> (16 * (e & 1))), C + (size_t)(mb + em) * N + n + e);
+                store_c(C + (size_t)(mb + em) * N + n + e, (uint16_t)(v[e >> 1] >> (16 * (e & 1))), tr.release);
           }
         }
         __builtin_amdgcn_sched_barrier(0);

@@ -280,7 +280,6 @@ void counter_hook_pair(const Launcher &L, int i, uint32_t gemm_grid, uint32_t *t
   hc->ack = ack + i;
   hc->err = err;
   hc->wait_target = (L.g.M > 0 && L.g.N > 0) ? gemm_grid : 0u;
-  hc->acquire = L.own ? 1u : 0u;
 }
 
 void counter_hooks(const Launcher &L, int n, uint32_t gemm_grid, uint32_t *tk, uint32_t *ack, uint32_t *err,

@@ -39,3 +39,27 @@ def test_large_tile_edges(layout, M, N, K):
     for cap in (0, 1):  # one workgroup per tile, and one that walks all tiles
         got, ref = int_gemm(M, N, K, layout, variant, cap, seed=M + K)
         assert np.array_equal(got, ref), cap
+
+
+# the collective reads each GEMM's output through the device counter while the
+# next GEMM runs: every tile kernel's device-scope stores, wide and narrow rows
+@pytest.mark.parametrize("layout,variant,M,N,K", [
+    ("kn", 32, 520, 264, 128), ("nk", 16, 520, 264, 128), ("nk", 16, 264, 129, 72), ("kn", 35, 264, 200, 72),
+    ("nk", 14, 264, 129, 72), ("kn", 39, 72, 136, 64), ("nk", 9, 72, 133, 64), ("kn", 37, 72, 136, 64),
+    ("nk", 7, 72, 133, 64), ("kn", 33, 16, 264, 136), ("nk", 21, 8, 133, 136), ("nk", 34, 16, 100, 1024)])
+def test_collective_reads_the_gemm_output(layout, variant, M, N, K):
+    n = 4
+    g = torch.Generator().manual_seed(M + N)
+    A = torch.randint(-2, 3, (M, K), generator=g).to(torch.bfloat16)
+    B = torch.randint(-2, 3, (K, N) if layout == "kn" else (N, K), generator=g).to(torch.bfloat16)
+    peers = torch.randint(-4, 5, (2, M * N), generator=g).float()
+    ref = oracle.gemm_bf16(A, B, M, N, K, b_layout=layout)
+    C = torch.full((n, M, N), float("nan"), device=DEV, dtype=torch.bfloat16)
+    out = torch.full((M * N,), float("nan"), device=DEV)
+    occ.run_overlap(A.to(DEV), B.to(DEV), C, bufs=peers.to(DEV), out=out, n_iter=n, reps=1, warmup=0,
+                    flags=occ.OCC_RUN_OVL, gemm_variant=variant, b_layout=layout, reduce_own=True, dep="counter")
+    torch.cuda.synchronize()
+    for i in range(n):
+        assert np.array_equal(bf16_bits(C[i]), ref), i
+    own = (ref.astype(np.uint32) << 16).view(np.float32).reshape(-1)
+    assert np.array_equal(out.cpu().numpy(), own + peers[0].numpy() + peers[1].numpy())
