@@ -22,9 +22,17 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+// the same at the alignment of their elements (one load or store all the same)
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2_a2 __attribute__((ext_vector_type(2), aligned(2)));
 
 // bf16 bit pattern -> binary32 (exact: the bf16 bits are the high half)
 __device__ __forceinline__ float widen_bf16(uint32_t bits16) { return __builtin_bit_cast(float, bits16 << 16); }
+
+// One own term, read at device scope (see reduce_vec_kernel).
+__device__ __forceinline__ float widen_own(const uint16_t *p) {
+  return widen_bf16(__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
 
 // Workgroup sizes.  The chunk sum runs two waves per workgroup: at the
 // default grid of one workgroup per CU, two of a CU's four SIMDs carry a comm
@@ -44,24 +52,39 @@ struct ChunkPtrs {
   const float *p[kMaxReduceChunks];
 };
 
-// Vector path: all chunk pointers and out are 16-byte aligned.  Element j's
-// sum is acc = c0[j]; acc = acc + c1[j]; ... exactly in chunk order; the
-// loads of all chunks for UNROLL positions are issued before any addition.
-// Measured on MI355X: for 8 terms, two positions per trip (16 loads in
-// flight per lane, 64 VGPRs) stream as fast as one in the isolated pass and
-// make the overlapped 8192^3 schedule 1-2 % shorter (the own-term reduce
-// 6 % faster); four positions fall in between.  The default grid is one
-// workgroup per CU.  At most 64 VGPRs (8 waves per SIMD): what the 256x256
-// GEMM's two waves leave of a SIMD's 512, so that both fit on one CU.
+// Vector path.  Element j's sum is acc = c0[j]; acc = acc + c1[j]; ... exactly
+// in chunk order; the loads of all chunks for UNROLL positions are issued
+// before any addition.  A position is 4 elements, loaded with one 16-byte load
+// per chunk at the element's own 4-byte alignment: chunks are often rows of
+// one buffer, and with an odd row length each starts at another offset from a
+// 16-byte boundary (a misaligned wave reads 9 lines instead of 8).  The
+// launcher starts positions where `out` is 16-byte aligned; the elements before
+// and after (`head` and the remainder, at most 6) go to the last workgroup's
+// first lanes.
+//
+// What bounds it is bytes in flight: the default grid is one workgroup of two
+// waves per CU, so a lane needs 12-16 loads outstanding.  NC >= 0 (the number
+// of fp32 chunks) therefore has its own instantiation for every term count up
+// to 16, with UNROLL from reduce_unroll; NC < 0 folds `nchunks` chunks in
+// batches of 8 loads.  Measured on MI355X at 0.5 GB of chunks, 256 workgroups:
+// batches of 8 reach 2.7 / 3.5 / 3.8 / 3.6 TB/s with 3 / 5 / 6 / 12 terms, the
+// exact counts 5.5-6.2; 6 x 11 000 003 as rows of one buffer took 700 us an
+// element at a time and takes 54.  At most 64 VGPRs: what the 256x256 GEMM's
+// two waves leave of a SIMD's 512, so that both fit on one CU.
 //
 // OWN: the first term is a bf16 buffer (this GPU's own contribution, e.g. its
-// GEMM output), widened exactly to binary32; the NC (or nchunks) fp32 chunks
-// follow it in order.  Its 8 bytes per position are one load.
-template <int NC, int UNROLL, bool OFF32, bool OWN>
+// GEMM output), widened exactly to binary32; the chunks follow it in order.
+// Its 8 bytes per position are one load, of device scope (kOwnDevice: the GEMM
+// that wrote them may have ended on another XCD while this kernel waited for
+// it, KHooks; the buffer is then 8-byte aligned) or an ordinary one at 2-byte
+// alignment (kOwnPlain).
+enum { kOwnNone = 0, kOwnDevice = 1, kOwnPlain = 2 };
+
+template <int NC, int UNROLL, bool OFF32, int OWN>
 __global__ __launch_bounds__(kReduceThreads) void reduce_vec_kernel(ChunkPtrs cp, int nchunks, size_t nvec,
                                                                     float *__restrict__ out,
-                                                                    const uint16_t *__restrict__ own, int prio,
-                                                                    uint32_t pace, KHooks tr) {
+                                                                    const uint16_t *__restrict__ own, int head,
+                                                                    int tail, int prio, uint32_t pace, KHooks tr) {
   // OFF32: every byte offset the loop forms fits in 32 bits (checked by the
   // host), so each access is a scalar base plus one shared 32-bit lane
   // offset instead of a 64-bit address per chunk: fewer vector instructions
@@ -70,23 +93,26 @@ __global__ __launch_bounds__(kReduceThreads) void reduce_vec_kernel(ChunkPtrs cp
   set_wave_priority(prio);
   const HookStart t0 = hooks_begin(tr);
   Pacer pc = pace_start(pace);
-  const int nc = NC > 0 ? NC : nchunks;
   const I n = (I)nvec;
   const I stride = (I)gridDim.x * kReduceThreads;
   I i = (I)blockIdx.x * kReduceThreads + threadIdx.x;
   auto ld = [&](int c, I k) {
     return __builtin_nontemporal_load(
-        reinterpret_cast<const f32x4 *>(reinterpret_cast<const char *>(cp.p[c]) + k * (I)sizeof(f32x4)));
+        reinterpret_cast<const f32x4_a4 *>(reinterpret_cast<const char *>(cp.p[c]) + k * (I)sizeof(f32x4)));
   };
   auto st = [&](f32x4 v, I k) {
-    __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(reinterpret_cast<char *>(out) + k * (I)sizeof(f32x4)));
+    __builtin_nontemporal_store(v, reinterpret_cast<f32x4_a4 *>(reinterpret_cast<char *>(out) + k * (I)sizeof(f32x4)));
   };
   auto ld_own = [&](I k) {
-    // device-scope: written by a GEMM that may still be running (KHooks)
-    const uint64_t d = __hip_atomic_load(
-        reinterpret_cast<const uint64_t *>(reinterpret_cast<const char *>(own) + k * (I)sizeof(uint64_t)),
-        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const u32x2 w = {(uint32_t)d, (uint32_t)(d >> 32)};
+    const char *p = reinterpret_cast<const char *>(own) + k * (I)sizeof(uint64_t);
+    u32x2 w;
+    if constexpr (OWN == kOwnDevice) {
+      const uint64_t d = __hip_atomic_load(reinterpret_cast<const uint64_t *>(p), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+      w = u32x2{(uint32_t)d, (uint32_t)(d >> 32)};
+    } else {
+      w = __builtin_nontemporal_load(reinterpret_cast<const u32x2_a2 *>(p));
+    }
     f32x4 r;
     r[0] = widen_bf16(w[0] & 0xFFFFu);
     r[1] = widen_bf16(w[0] >> 16);
@@ -94,72 +120,79 @@ __global__ __launch_bounds__(kReduceThreads) void reduce_vec_kernel(ChunkPtrs cp
     r[3] = widen_bf16(w[1] >> 16);
     return r;
   };
+  auto add = [](f32x4 a, f32x4 b) {
+    a[0] = a[0] + b[0];
+    a[1] = a[1] + b[1];
+    a[2] = a[2] + b[2];
+    a[3] = a[3] + b[3];
+    return a;
+  };
   constexpr int C0 = OWN ? 0 : 1;  // first fp32 chunk added to the first term
 
-  if constexpr (NC > 0) {
-    for (bool first = true; i + (UNROLL - 1) * stride < n; i += UNROLL * stride, first = false) {
-      if (!first) pace_wait(pc);
-      f32x4 v[NC][UNROLL], o[UNROLL];
+  if constexpr (NC >= 0) {
+    auto trip = [&](auto positions) {
+      constexpr int U = decltype(positions)::value;
+      f32x4 v[NC > 0 ? NC : 1][U], o[U];
       if constexpr (OWN) {
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) o[u] = ld_own(i + u * stride);
+        for (int u = 0; u < U; ++u) o[u] = ld_own(i + u * stride);
       }
 #pragma unroll
       for (int c = 0; c < NC; ++c)
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) v[c][u] = ld(c, i + u * stride);
+        for (int u = 0; u < U; ++u) v[c][u] = ld(c, i + u * stride);
 #pragma unroll
-      for (int u = 0; u < UNROLL; ++u) {
+      for (int u = 0; u < U; ++u) {
         f32x4 acc = OWN ? o[u] : v[0][u];
 #pragma unroll
-        for (int c = C0; c < NC; ++c) {
-          acc[0] = acc[0] + v[c][u][0];
-          acc[1] = acc[1] + v[c][u][1];
-          acc[2] = acc[2] + v[c][u][2];
-          acc[3] = acc[3] + v[c][u][3];
-        }
+        for (int c = C0; c < NC; ++c) acc = add(acc, v[c][u]);
         st(acc, i + u * stride);
       }
+    };
+    for (bool first = true; i + (UNROLL - 1) * stride < n; i += UNROLL * stride, first = false) {
+      if (!first) pace_wait(pc);
+      trip(std::integral_constant<int, UNROLL>{});
+    }
+    if constexpr (UNROLL > 1)
+      for (; i < n; i += stride) trip(std::integral_constant<int, 1>{});
+  } else {
+    // chunk count known at run time: batches of 8 loads, folded in order
+    for (bool first = true; i < n; i += stride, first = false) {
+      if (!first) pace_wait(pc);
+      f32x4 acc = OWN ? ld_own(i) : ld(0, i);
+      for (int c0 = C0; c0 < nchunks; c0 += 8) {
+        f32x4 v[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c)
+          if (c0 + c < nchunks) v[c] = ld(c0 + c, i);
+#pragma unroll
+        for (int c = 0; c < 8; ++c)
+          if (c0 + c < nchunks) acc = add(acc, v[c]);
+      }
+      st(acc, i);
     }
   }
-  // Remaining positions (and every position when the chunk count is only
-  // known at run time): chunks in batches of 8 loads, folded in order.
-  for (bool first = true; i < n; i += stride, first = false) {
-    if (NC == 0 && !first) pace_wait(pc);
-    f32x4 acc = OWN ? ld_own(i) : ld(0, i);
-    for (int c0 = C0; c0 < nc; c0 += 8) {
-      f32x4 v[8];
-#pragma unroll
-      for (int c = 0; c < 8; ++c)
-        if (c0 + c < nc) v[c] = ld(c0 + c, i);
-#pragma unroll
-      for (int c = 0; c < 8; ++c)
-        if (c0 + c < nc) {
-          acc[0] = acc[0] + v[c][0];
-          acc[1] = acc[1] + v[c][1];
-          acc[2] = acc[2] + v[c][2];
-          acc[3] = acc[3] + v[c][3];
-        }
-    }
-    st(acc, i);
+  if (blockIdx.x == gridDim.x - 1 && (int)threadIdx.x < head + tail) {
+    const ptrdiff_t j = (int)threadIdx.x < head ? (ptrdiff_t)threadIdx.x - head
+                                                : (ptrdiff_t)(nvec * 4) + (ptrdiff_t)threadIdx.x - head;
+    float acc = OWN ? widen_own(own + j) : cp.p[0][j];
+    for (int c = C0; c < nchunks; ++c) acc = acc + cp.p[c][j];
+    out[j] = acc;
   }
   hooks_end(tr, t0);
 }
 
-// Scalar path: elements [first, len) one at a time (the tail after the vector
-// path, or everything when a buffer is not 16-byte aligned).
-__global__ __launch_bounds__(kReduceThreads) void reduce_scalar_kernel(ChunkPtrs cp, int nchunks,
-                                                                       size_t first, size_t len,
+// Scalar path, one element at a time: for fp32 buffers that are not even
+// 4-byte aligned.
+__global__ __launch_bounds__(kReduceThreads) void reduce_scalar_kernel(ChunkPtrs cp, int nchunks, size_t len,
                                                                        float *__restrict__ out,
                                                                        const uint16_t *__restrict__ own,
                                                                        int prio, KHooks tr) {
   set_wave_priority(prio);
   const HookStart t0 = hooks_begin(tr);
   const size_t stride = (size_t)gridDim.x * kReduceThreads;
-  for (size_t j = first + (size_t)blockIdx.x * kReduceThreads + threadIdx.x; j < len; j += stride) {
-    float acc = own != nullptr
-                    ? widen_bf16(__hip_atomic_load(own + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-                    : cp.p[0][j];
+  for (size_t j = (size_t)blockIdx.x * kReduceThreads + threadIdx.x; j < len; j += stride) {
+    float acc = own != nullptr ? widen_own(own + j) : cp.p[0][j];
     for (int c = own != nullptr ? 0 : 1; c < nchunks; ++c) acc = acc + cp.p[c][j];
     out[j] = acc;
   }
@@ -247,10 +280,15 @@ int clamp_wgs(size_t work_units, int wanted, int threads) {
 
 // Positions per lane per trip of the vector chunk sum for a number of terms
 // (fp32 chunks plus the own term); the launch table and the pacing period
-// both take it from here.  With 64-bit offsets two positions of 8 terms would
-// need more than the 64 VGPRs that fit beside the 256x256 GEMM's waves.
+// both take it from here.  12-16 loads in flight per lane as far as 64 VGPRs
+// hold them; 64-bit offsets need registers of their own.
+constexpr int kExactTerms = 16;  // term counts with an instantiation of their own
+constexpr bool exact_terms(int terms, bool off32) {
+  return off32 ? terms <= kExactTerms : (terms == 2 || terms == 4 || terms == 8 || terms == 16);
+}
 constexpr int reduce_unroll(int terms, bool off32) {
-  return terms == 2 ? 4 : (terms == 4 || (terms == 8 && off32)) ? 2 : 1;
+  if (!exact_terms(terms, off32)) return 1;
+  return terms <= 3 ? 4 : terms == 4 ? 2 : (terms <= 8 && off32) ? 2 : 1;
 }
 
 // Loads in flight per lane of the vector permutation (launch, pacing and the
@@ -271,16 +309,22 @@ uint32_t pace_ticks(double trip_bytes, double rate_gbs) {
 
 }  // namespace
 
-template <bool OFF32, bool OWN>
+// Launch with the instantiation of c.nchunks (+ own) terms, T counting up.
+template <bool OFF32, int OWN, int T = 1>
 void launch_reduce(int nchunks, int g, hipStream_t s, const ChunkPtrs &cp, size_t nvec, float *out,
-                   const uint16_t *own, int prio, uint32_t pace, const KHooks &tr) {
-  // instantiations by the number of terms (own + fp32 chunks)
-  switch (nchunks + (OWN ? 1 : 0)) {
-    case 2: hipLaunchKernelGGL((reduce_vec_kernel<OWN ? 1 : 2, reduce_unroll(2, OFF32), OFF32, OWN>), dim3(g), dim3(kReduceThreads), 0, s, cp, nchunks, nvec, out, own, prio, pace, tr); break;
-    case 4: hipLaunchKernelGGL((reduce_vec_kernel<OWN ? 3 : 4, reduce_unroll(4, OFF32), OFF32, OWN>), dim3(g), dim3(kReduceThreads), 0, s, cp, nchunks, nvec, out, own, prio, pace, tr); break;
-    case 8: hipLaunchKernelGGL((reduce_vec_kernel<OWN ? 7 : 8, reduce_unroll(8, OFF32), OFF32, OWN>), dim3(g), dim3(kReduceThreads), 0, s, cp, nchunks, nvec, out, own, prio, pace, tr); break;
-    case 16: hipLaunchKernelGGL((reduce_vec_kernel<OWN ? 15 : 16, reduce_unroll(16, OFF32), OFF32, OWN>), dim3(g), dim3(kReduceThreads), 0, s, cp, nchunks, nvec, out, own, prio, pace, tr); break;
-    default: hipLaunchKernelGGL((reduce_vec_kernel<0, 1, OFF32, OWN>), dim3(g), dim3(kReduceThreads), 0, s, cp, nchunks, nvec, out, own, prio, pace, tr); break;
+                   const uint16_t *own, int head, int tail, int prio, uint32_t pace, const KHooks &tr) {
+  if constexpr (T > kExactTerms) {
+    hipLaunchKernelGGL((reduce_vec_kernel<-1, 1, OFF32, OWN>), dim3(g), dim3(kReduceThreads), 0, s, cp, nchunks, nvec,
+                       out, own, head, tail, prio, pace, tr);
+  } else {
+    if constexpr (exact_terms(T, OFF32)) {
+      if (nchunks + (OWN ? 1 : 0) == T) {
+        hipLaunchKernelGGL((reduce_vec_kernel<T - (OWN ? 1 : 0), reduce_unroll(T, OFF32), OFF32, OWN>), dim3(g),
+                           dim3(kReduceThreads), 0, s, cp, nchunks, nvec, out, own, head, tail, prio, pace, tr);
+        return;
+      }
+    }
+    launch_reduce<OFF32, OWN, T + 1>(nchunks, g, s, cp, nvec, out, own, head, tail, prio, pace, tr);
   }
 }
 
@@ -295,48 +339,48 @@ int reduce_launch(const ReduceCall &c, hipStream_t s) {
   ChunkPtrs cp;
   memset(&cp, 0, sizeof cp);
   const bool own = c.own != nullptr;
-  bool vec = aligned16(c.out) && (!own || (reinterpret_cast<uintptr_t>(c.own) & 7u) == 0);
+  auto aligned = [](const void *p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; };
+  bool vec = aligned(c.out, 4) && aligned(c.own, 2);
   for (int i = 0; i < c.nchunks; ++i) {
     cp.p[i] = c.bufs[i];
-    vec = vec && aligned16(c.bufs[i]);
+    vec = vec && aligned(c.bufs[i], 4);
   }
-  int wgs = c.wgs > 0 ? c.wgs : reduce_default_wgs(c);
+  const int wgs = c.wgs > 0 ? c.wgs : reduce_default_wgs(c);
   const int prio = c.priority;
-  // a dependency wait is acknowledged by every workgroup of every kernel below
+  // a dependency wait is acknowledged by every workgroup of the kernel
   KHooks tr = c.trace;
-  if (vec) {
-    size_t nvec = c.len / 4;
-    const bool tail = nvec * 4 < c.len;
-    if (tr.wait != nullptr)
-      tr.ack_target = (nvec > 0 ? (uint32_t)clamp_wgs(nvec, wgs, kReduceThreads) : 0u) + (tail ? 1u : 0u);
-    if (nvec > 0) {
-      int g = clamp_wgs(nvec, wgs, kReduceThreads);
-      const int terms = c.nchunks + (own ? 1 : 0);
-      // 32-bit offsets when the largest byte offset the loop can form, (nvec
-      // plus one unrolled grid stride) * 16, stays below 2^32
-      const bool off32 = ((double)nvec + 4.0 * g * kReduceThreads) * 16.0 < 4294967296.0;
-      // positions per lane per trip of each instantiation, and the bytes
-      // one position moves
-      const int unroll = reduce_unroll(terms, off32);
-      const double pos_bytes = 16.0 * (c.nchunks + 1) + (own ? 8.0 : 0.0);
-      const uint32_t pace = pace_ticks((double)g * kReduceThreads * unroll * pos_bytes, c.rate_gbs);
-      if (own) {
-        if (off32) launch_reduce<true, true>(c.nchunks, g, s, cp, nvec, c.out, c.own, prio, pace, tr);
-        else launch_reduce<false, true>(c.nchunks, g, s, cp, nvec, c.out, c.own, prio, pace, tr);
-      } else {
-        if (off32) launch_reduce<true, false>(c.nchunks, g, s, cp, nvec, c.out, nullptr, prio, pace, tr);
-        else launch_reduce<false, false>(c.nchunks, g, s, cp, nvec, c.out, nullptr, prio, pace, tr);
-      }
-    }
-    if (tail)
-      hipLaunchKernelGGL(reduce_scalar_kernel, dim3(1), dim3(kReduceThreads), 0, s, cp, c.nchunks, nvec * 4,
-                         c.len, c.out, c.own, prio, tr);
-  } else {
+  if (!vec) {
     const int g = clamp_wgs(c.len, wgs, kReduceThreads);
     if (tr.wait != nullptr) tr.ack_target = (uint32_t)g;
-    hipLaunchKernelGGL(reduce_scalar_kernel, dim3(g), dim3(kReduceThreads), 0, s, cp,
-                       c.nchunks, (size_t)0, c.len, c.out, c.own, prio, tr);
+    hipLaunchKernelGGL(reduce_scalar_kernel, dim3(g), dim3(kReduceThreads), 0, s, cp, c.nchunks, c.len, c.out,
+                       c.own, prio, tr);
+    return hipGetLastError() == hipSuccess ? OCC_OK : OCC_EHIP;
   }
+  // positions start at out's first 16-byte boundary; with an own term at
+  // element 0, which keeps its 8-byte loads aligned
+  size_t head = own ? 0 : ((16 - (reinterpret_cast<uintptr_t>(c.out) & 15)) & 15) / 4;
+  if (head > c.len) head = c.len;
+  for (int i = 0; i < c.nchunks; ++i) cp.p[i] += head;
+  const size_t nvec = (c.len - head) / 4;
+  const int tail = (int)(c.len - head - nvec * 4);
+  const int g = clamp_wgs(nvec, wgs, kReduceThreads);
+  if (tr.wait != nullptr) tr.ack_target = (uint32_t)g;
+  const int terms = c.nchunks + (own ? 1 : 0);
+  // 32-bit offsets when the largest byte offset the loop can form, (nvec
+  // plus one unrolled grid stride) * 16, stays below 2^32
+  const bool off32 = ((double)nvec + 4.0 * g * kReduceThreads) * 16.0 < 4294967296.0;
+  // the bytes one position moves
+  const double pos_bytes = 16.0 * (c.nchunks + 1) + (own ? 8.0 : 0.0);
+  const uint32_t pace = pace_ticks((double)g * kReduceThreads * reduce_unroll(terms, off32) * pos_bytes, c.rate_gbs);
+  float *out = c.out + head;
+  auto launch = [&](auto mode) {
+    constexpr int OWN = decltype(mode)::value;
+    if (off32) launch_reduce<true, OWN>(c.nchunks, g, s, cp, nvec, out, c.own, (int)head, tail, prio, pace, tr);
+    else launch_reduce<false, OWN>(c.nchunks, g, s, cp, nvec, out, c.own, (int)head, tail, prio, pace, tr);
+  };
+  if (!own) launch(std::integral_constant<int, kOwnNone>{});
+  else if (aligned(c.own, 8)) launch(std::integral_constant<int, kOwnDevice>{});
+  else launch(std::integral_constant<int, kOwnPlain>{});
   return hipGetLastError() == hipSuccess ? OCC_OK : OCC_EHIP;
 }
 

@@ -63,3 +63,45 @@ def test_collective_reads_the_gemm_output(layout, variant, M, N, K):
         assert np.array_equal(bf16_bits(C[i]), ref), i
     own = (ref.astype(np.uint32) << 16).view(np.float32).reshape(-1)
     assert np.array_equal(out.cpu().numpy(), own + peers[0].numpy() + peers[1].numpy())
+
+
+def f32_at(values, offset):
+    """A GPU copy of `values` starting `offset` elements past a 16-byte boundary."""
+    buf = torch.full((values.numel() + 8,), float("nan"), device=DEV, dtype=values.dtype)
+    assert buf.data_ptr() % 16 == 0
+    v = buf[offset:offset + values.numel()]
+    v.copy_(values)
+    return v
+
+
+# every exact term count and the batched ones, one to a few positions per lane,
+# chunks and output each at its own offset from a 16-byte boundary
+@pytest.mark.parametrize("terms", list(range(1, 18)) + [64])
+@pytest.mark.parametrize("length", [1, 3, 6, 515, 4099, 262151])
+def test_chunk_sum_terms_and_alignments(terms, length):
+    if length > 5000 and terms > 17:
+        length = 5003
+    g = torch.Generator().manual_seed(terms * 1000 + length)
+    x = torch.rand((terms, length), generator=g) * 2 - 1
+    for shift in (0, 1, 3):
+        bufs = [f32_at(x[c], (c + shift) % 4) if shift else x[c].to(DEV) for c in range(terms)]
+        out = f32_at(torch.zeros(length), shift)
+        occ.share_reduce(bufs, out, wgs=3 if length > 200000 else 0)
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy().view(np.uint32), oracle.chunk_sum_f32(x.numpy()).view(np.uint32)), shift
+
+
+@pytest.mark.parametrize("peers", [0, 1, 2, 6, 15, 16, 63])
+@pytest.mark.parametrize("length", [1, 7, 515, 66053])
+def test_own_chunk_sum_terms_and_alignments(peers, length):
+    g = torch.Generator().manual_seed(peers * 1000 + length)
+    own = torch.randn(length, generator=g).to(torch.bfloat16)
+    x = torch.rand((peers, length), generator=g) * 2 - 1
+    want = own.float()
+    for c in range(peers):
+        want = want + x[c]
+    for shift in (0, 1, 2):  # own at 16-, 2- and 4-byte alignment
+        out = f32_at(torch.zeros(length), shift)
+        occ.share_reduce_own(f32_at(own, shift), [f32_at(x[c], (c + shift) % 4) for c in range(peers)], out)
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy().view(np.uint32), want.numpy().view(np.uint32)), shift
