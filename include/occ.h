@@ -178,7 +178,7 @@ int occ_gemm_info(int *tile_lds_bytes, int *max_lds_per_wg, int *lds_per_cu);
  * definition (no reassociation, no contraction, denormals kept).
  *   bufs    : HOST array of nchunks device pointers, 1 <= nchunks <= 64.
  *   out     : device fp32 buffer of len elements; must not overlap any bufs[c].
- * len == 0 is a no-op.  Any alignment is accepted; 16-byte-aligned buffers
+ * len == 0 is a no-op.  Any alignment is accepted; 4-byte-aligned buffers
  * take the vectorised path.
  */
 int share_reduce(const float *const *bufs, int nchunks, size_t len, float *out, void *stream);
@@ -201,8 +201,8 @@ int share_reduce_ex(const float *const *bufs, int nchunks, size_t len, float *ou
  *          1 <= nchunks <= 512.
  *   src, dst : device buffers of nchunks*chunk_bytes bytes; must not overlap.
  * nchunks is an addition to the three-pointer form: the length of perm.
- * chunk_bytes == 0 is a no-op.  16-byte-aligned src, dst and chunk_bytes take
- * the vectorised path; anything else is copied byte by byte.
+ * chunk_bytes == 0 is a no-op.  Any alignment of src, dst and chunk_bytes is
+ * copied 16 bytes at a time.
  */
 int share_permute(const void *src, void *dst, const int32_t *perm, int nchunks, size_t chunk_bytes,
                   void *stream);
@@ -219,8 +219,8 @@ int share_permute(const void *src, void *dst, const int32_t *perm, int nchunks, 
  *   out   : device fp32 buffer of len elements; must not overlap own or any
  *           peer.
  *   wgs, priority : as share_reduce_ex.
- * len == 0 is a no-op.  own 8-byte aligned with out and peers 16-byte aligned
- * takes the vectorised path.
+ * len == 0 is a no-op.  Buffers aligned to their elements take the vectorised
+ * path.
  */
 int share_reduce_own(const void *own, const float *const *peers, int npeers, size_t len, float *out,
                      int wgs, int priority, void *stream);

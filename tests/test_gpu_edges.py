@@ -105,3 +105,23 @@ def test_own_chunk_sum_terms_and_alignments(peers, length):
         occ.share_reduce_own(f32_at(own, shift), [f32_at(x[c], (c + shift) % 4) for c in range(peers)], out)
         torch.cuda.synchronize()
         assert np.array_equal(out.cpu().numpy().view(np.uint32), want.numpy().view(np.uint32)), shift
+
+
+# chunk sizes around 16 bytes and around a workgroup's round, source and
+# destination at their own byte offsets; nothing outside the destination changes
+@pytest.mark.parametrize("nchunks,chunk_bytes", [(1, 1), (5, 15), (3, 16), (7, 17), (512, 31), (33, 1000), (3, 16384),
+                                                 (2, 16400), (5, 40001), (3, 300003), (300, 20480), (4, 1 << 20)])
+def test_permute_alignments(nchunks, chunk_bytes):
+    g = torch.Generator().manual_seed(chunk_bytes)
+    src = torch.randint(0, 256, (nchunks * chunk_bytes,), generator=g, dtype=torch.uint8)
+    perm = torch.randperm(nchunks, generator=g).to(torch.int32)
+    want = oracle.permute_chunks(src.numpy(), perm.numpy(), chunk_bytes)
+    for so, do in ((0, 0), (1, 0), (0, 3), (8, 15), (2, 2)):
+        s = torch.zeros(src.numel() + 32, dtype=torch.uint8, device=DEV)
+        s[so:so + src.numel()] = src.to(DEV)
+        d = torch.full((src.numel() + 64,), 77, dtype=torch.uint8, device=DEV)
+        view = d[16 + do:16 + do + src.numel()]
+        occ.share_permute(s[so:so + src.numel()], view, perm, chunk_bytes, wgs=0 if do else 5)
+        torch.cuda.synchronize()
+        assert np.array_equal(view.cpu().numpy(), want), (so, do)
+        assert (d[:16 + do] == 77).all() and (d[16 + do + src.numel():] == 77).all(), (so, do)
