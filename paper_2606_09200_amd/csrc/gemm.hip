@@ -11,20 +11,23 @@
 // reads) or N x K (occ_gemm_bt: C = A * B^T, a linear layer's weight layout,
 // both MFMA operands read from LDS as 16-byte rows).
 //
-// The kernels live in gemm_pp.h (256x256 tiles, both layouts), gemm_dl.h
-// (smaller direct-to-LDS tiles, both layouts),
+// The kernels live in gemm_pp.h (256x256 tiles, both layouts), gemm_rp.h
+// (register-pipelined smaller tiles, both layouts), gemm_dl.h (the paper's and
+// other direct-to-LDS tiles, both layouts),
 // gemm_tiled.h (register-staged tiles, the paper's opt1/opt2 with B N x K),
 // gemm_skinny.h and gemm_skinny_ldsb.h (M <= 16, B N x K) and
 // gemm_skinny_kn.h (M <= 16, B K x N); this file holds the variant table, the
 // launch plan and the launcher.
 #include "gemm_dl.h"
 #include "gemm_pp.h"
+#include "gemm_rp.h"
 #include "gemm_skinny.h"
 #include "gemm_skinny_kn.h"
 #include "gemm_skinny_ldsb.h"
 #include "gemm_tiled.h"
 
 #include <algorithm>
+#include <cmath>
 
 namespace occ {
 namespace {
@@ -47,11 +50,13 @@ struct Variant {
   bool b_kn;         // takes B stored K x N (and only that)
   int nmax;          // largest N the kernel takes (0 = any)
   int per_cu;        // skinny kernels: persistent workgroups per CU (0 = 1)
+  TiledFn fn_nt;     // the same with B's loads non-temporal, where the kernel has that form
 };
 
 template <class T>
 constexpr Variant make_variant(int id, const char *name) {
-  return Variant{id, T::BM, T::BN, T::BK, T::NT, T::LDS_BYTES, gemm_tiled_kernel<T>, nullptr, name, 0, 0, false, 0};
+  return Variant{id, T::BM, T::BN, T::BK, T::NT, T::LDS_BYTES, gemm_tiled_kernel<T>, nullptr, name, 0, 0, false, 0, 0,
+                 nullptr};
 }
 
 // The direct-to-LDS kernel addresses an operand tile with 32-bit byte
@@ -72,20 +77,33 @@ constexpr int dl_nmax() {
 template <class T>
 constexpr Variant make_dl_variant(int id, const char *name) {
   return Variant{id, T::BM, T::BN, T::BK, T::NT, T::LDS_BYTES, gemm_dl_kernel<T>, nullptr, name,
-                 dl_kmax<T>(), 0, T::BKN, dl_nmax<T>()};
+                 dl_kmax<T>(), 0, T::BKN, dl_nmax<T>(), 0, nullptr};
 }
 
 // The two-group kernel addresses its operands in the same way.
 template <class T>
 constexpr Variant make_pp_variant(int id, const char *name) {
   return Variant{id, T::BM, T::BN, T::BK, T::NT, T::LDS_BYTES, gemm_pp_kernel<T>, nullptr, name,
-                 dl_kmax<T>(), 0, T::BKN, dl_nmax<T>()};
+                 dl_kmax<T>(), 0, T::BKN, dl_nmax<T>(), 0, nullptr};
+}
+
+// So do the register-pipelined tiles; NT also has the form with non-temporal B.
+template <class T, class NT>
+constexpr Variant make_rp_variant(int id, const char *name) {
+  return Variant{id, T::BM, T::BN, T::BK, T::NT, T::LDS_BYTES, gemm_rp_kernel<T>, nullptr, name,
+                 dl_kmax<T>(), 0, T::BKN, dl_nmax<T>(), 0, gemm_rp_kernel<NT>};
+}
+template <class T>
+constexpr Variant make_rp_variant(int id, const char *name) {
+  Variant v = make_rp_variant<T, T>(id, name);
+  v.fn_nt = nullptr;
+  return v;
 }
 
 template <int WAVES, int UNROLL>
 constexpr Variant make_skinny_variant(int id, const char *name) {
   return Variant{id, 16, 16, kSkinnyKB * UNROLL, 64 * WAVES, (WAVES - 1) * 64 * 16, nullptr,
-                 gemm_skinny_kernel<WAVES, UNROLL>, name, 0, 0, false, 0};
+                 gemm_skinny_kernel<WAVES, UNROLL>, name, 0, 0, false, 0, 0, nullptr};
 }
 
 // A K x N B block (32 rows of N) is addressed with 32-bit offsets from its
@@ -95,7 +113,7 @@ template <int WAVES, int STAGES, int COLS>
 constexpr Variant make_skinny_kn_variant(int id, const char *name) {
   return Variant{id, 16, COLS, kSknKB, 64 * WAVES, SkinnyKn<WAVES, STAGES, COLS>::LDS_BYTES, nullptr,
                  gemm_skinny_kn_kernel<WAVES, STAGES, COLS>, name, (int)((0x80000000ull / 32u) & ~7ull), 0,
-                 true, (int)((0x80000000ull / (2u * kSknKB)) & ~7ull), 2};
+                 true, (int)((0x80000000ull / (2u * kSknKB)) & ~7ull), 2, nullptr};
 }
 
 // B staged through LDS in 128-k blocks, A in registers: K a multiple of
@@ -103,7 +121,8 @@ constexpr Variant make_skinny_kn_variant(int id, const char *name) {
 template <int WAVES, int STAGES, int KBW>
 constexpr Variant make_skinny_ldsb_variant(int id, const char *name) {
   return Variant{id, 16, 16, kSlbKB, 64 * WAVES, SkinnyLdsB<WAVES, STAGES, KBW>::LDS_BYTES, nullptr,
-                 gemm_skinny_ldsb_kernel<WAVES, STAGES, KBW>, name, 32 * WAVES * KBW, kSlbKB * WAVES, false, 0, 1};
+                 gemm_skinny_ldsb_kernel<WAVES, STAGES, KBW>, name, 32 * WAVES * KBW, kSlbKB * WAVES, false, 0, 1,
+                 nullptr};
 }
 
 // B stored N x K (occ_gemm_bt)
@@ -112,25 +131,36 @@ using T64x64_opt2 = Tile<64, 64, 64, 2, 2, 1>;   // Table 1 opt2: 64x64x64
 // the opt2 tile with two direct-to-LDS stages: the automatic choice for small
 // shapes (one k-step's DMA in flight while the previous one is used)
 using D64x64_4w_2s = Tile<64, 64, 64, 2, 2, 2>;
-using D128x128_4w_3s = Tile<128, 128, 64, 2, 2, 3>;
 // two workgroups per CU: each has its own barriers, so one computes while the
 // other waits (48 KiB of LDS, 4 waves of 128x64 each)
 using P128x256k32_4w_2s = Tile<128, 256, 32, 1, 4, 2, true, 2>;
 
 // B stored K x N (occ_gemm): the same tiles with the B tile staged as stored
 // and its MFMA operands read with LDS transpose reads
-using KN128x128_4w_3s = Tile<128, 128, 64, 2, 2, 3, false, 1, true>;
 using KN64x64_opt1 = Tile<64, 64, 32, 2, 2, 1, false, 1, true>;   // Table 1 opt1, one stage
 using KN64x64_opt2 = Tile<64, 64, 64, 2, 2, 1, false, 1, true>;   // Table 1 opt2, one stage
 using KN64x64_4w_2s = Tile<64, 64, 64, 2, 2, 2, false, 1, true>;
 using PKN128x256k32_4w_2s = Tile<128, 256, 32, 1, 4, 2, true, 2, true>;
+
+// the register-pipelined tiles, both layouts
+template <bool BKN>
+using R256x128 = RpTile<256, 128, 64, 4, 2, 3, 1, BKN>;
+template <bool BKN, bool NTB = false>
+using R128x128 = RpTile<128, 128, 64, 2, 4, 3, 1, BKN, NTB>;
+template <bool BKN>
+using R128x64 = RpTile<128, 64, 64, 4, 2, 4, 2, BKN>;
+template <bool BKN>
+using R64x64k128 = RpTile<64, 64, 128, 2, 2, 4, 4, BKN>;
 
 const Variant kVariants[] = {
     // B stored N x K
     make_variant<T64x64_opt1>(6, "64x64x32 opt1, B N x K"),
     make_variant<T64x64_opt2>(7, "64x64x64 opt2, B N x K"),
     make_dl_variant<D64x64_4w_2s>(9, "dl 64x64x64 4w 2st, B N x K"),
-    make_dl_variant<D128x128_4w_3s>(14, "dl 128x128x64 4w 3st, B N x K"),
+    make_rp_variant<R256x128<false>>(10, "rp 256x128x64 8w 3st, B N x K"),
+    make_rp_variant<R128x64<false>>(11, "rp 128x64x64 8w 4st, B N x K"),
+    make_rp_variant<R64x64k128<false>>(12, "rp 64x64x128 4w 4st, B N x K"),
+    make_rp_variant<R128x128<false>, R128x128<false, true>>(14, "rp 128x128x64 8w 3st, B N x K"),
     make_pp_variant<PpTile<false>>(16, "pp 256x256x64 8w 2st, B N x K"),
     make_skinny_variant<8, 8>(21, "skinny M<=16, 8 waves, unroll 8, B N x K"),
     make_dl_variant<P128x256k32_4w_2s>(25, "dl+pipe 128x256x32 4w 2st 2wg/cu, B N x K"),
@@ -138,11 +168,14 @@ const Variant kVariants[] = {
     // B stored K x N
     make_pp_variant<PpTile<true>>(32, "pp 256x256x64 8w 2st, B K x N"),
     make_skinny_kn_variant<4, 2, 128>(33, "skinny M<=16, 128-column units, 4 waves, 2 LDS stages, B K x N"),
-    make_dl_variant<KN128x128_4w_3s>(35, "dl 128x128x64 4w 3st, B K x N"),
+    make_rp_variant<R128x128<true>, R128x128<true, true>>(35, "rp 128x128x64 8w 3st, B K x N"),
     make_dl_variant<KN64x64_opt1>(36, "dl 64x64x32 opt1 1st, B K x N"),
     make_dl_variant<KN64x64_opt2>(37, "dl 64x64x64 opt2 1st, B K x N"),
     make_dl_variant<PKN128x256k32_4w_2s>(38, "dl+pipe 128x256x32 4w 2st 2wg/cu, B K x N"),
     make_dl_variant<KN64x64_4w_2s>(39, "dl 64x64x64 4w 2st, B K x N"),
+    make_rp_variant<R256x128<true>>(40, "rp 256x128x64 8w 3st, B K x N"),
+    make_rp_variant<R128x64<true>>(41, "rp 128x64x64 8w 4st, B K x N"),
+    make_rp_variant<R64x64k128<true>>(42, "rp 64x64x128 4w 4st, B K x N"),
 };
 
 constexpr int kMaxVariantId = 63;  // launch-attribute caches are indexed by id
@@ -158,12 +191,44 @@ const Variant *find_variant(int id) {
 
 int ceil_div(long long a, long long b) { return (int)((a + b - 1) / b); }
 
-// The kernel for a shape: skinny for M <= 16, else the largest tile that
-// still gives at least one 256x256 tile per CU (or one 128x128 tile per two
-// CUs), else the 64x64x64 tile with two stages.  A K beyond what a
-// direct-to-LDS tile addresses with 32-bit offsets takes the 64x64 tile, and
-// beyond that (B N x K) the register-staged opt2 tile.
-int auto_variant(int M, int N, int K, int num_cus, bool b_kn) {
+// B too large for the 256 MB last-level cache.
+bool b_exceeds_llc(int N, int K) { return (long long)N * K * 2 > (256ll << 20); }
+
+// Estimated time (us) of a tile on a shape: the launch, then the rounds in which
+// `slots` workgroups at a time work off the tiles, each `fixed` (prologue,
+// epilogue) plus `step` per 64 of K.  The constants are the measured times of
+// single rounds on MI355X: 2048x2048x4096 takes one round of 128x128 tiles, 33.5
+// us = 3 + 2 + 64 * 0.44; 64x64 tiles of two small stages share a CU, so their
+// rounds need not be whole.  On 47 shapes of 64..8192 (M), 128..28672 (N) and
+// 128..8192 (K) in both layouts the choice is within 0.7 % of the fastest tile
+// on average (11 % at most), and 22 % faster than 256x256, 128x128 and 64x64
+// chosen by tile count alone.
+struct TileCost {
+  int id_nk, id_kn;
+  double launch, fixed, step;
+  bool shared;  // several workgroups per CU
+};
+const TileCost kTileCosts[] = {
+    {16, 32, 3.0, 4.0, 1.1, false},   // 256x256
+    {10, 40, 3.0, 2.5, 0.68, false},  // 256x128
+    {14, 35, 3.0, 2.0, 0.44, false},  // 128x128
+    {11, 41, 3.0, 1.6, 0.29, false},  // 128x64
+    {12, 42, 3.0, 1.6, 0.19, false},  // 64x64x128
+    {9, 39, 1.6, 0.4, 0.45, true},    // 64x64
+};
+
+// The kernel for a shape.  M <= 16: skinny.  A pad asks for a given residency
+// of the GEMM's workgroups, so with one the tile follows from the tile count
+// alone: the largest of 256x256, 128x128 and 64x64 that still gives one
+// 256x256 tile per CU or one 128x128 tile per two CUs.  Without one it is the
+// tile with the least estimated time, except that a B which is read once and
+// comes from memory goes to the 128x128 tile (whose loads can be non-temporal)
+// when that covers M: the tile then matters little, the loads much.  A K or N
+// beyond what the chosen tile addresses with 32-bit offsets takes the 64x64
+// tile, and a K beyond that (B N x K) the register-staged opt2 tile.
+int auto_variant(const GemmCall &c, int num_cus) {
+  const int M = c.M, N = c.N, K = c.K;
+  const bool b_kn = c.b_kn;
   if (M <= 16) {
     if (b_kn) return 33;
     // A kept in registers and B staged through LDS when K is whole
@@ -172,11 +237,29 @@ int auto_variant(int M, int N, int K, int num_cus, bool b_kn) {
     return 21;
   }
   const int large = b_kn ? 32 : 16, mid = b_kn ? 35 : 14, small = b_kn ? 39 : 9;
-  long long big = (long long)ceil_div(M, 256) * ceil_div(N, 256);
-  long long mids = (long long)ceil_div(M, 128) * ceil_div(N, 128);
-  int v = big >= num_cus ? large : (mids >= num_cus / 2 ? mid : small);
+  int v = small;
+  if (c.lds_bytes > 0) {
+    long long big = (long long)ceil_div(M, 256) * ceil_div(N, 256);
+    long long mids = (long long)ceil_div(M, 128) * ceil_div(N, 128);
+    v = big >= num_cus ? large : (mids >= num_cus / 2 ? mid : small);
+  } else if (M <= 128 && b_exceeds_llc(N, K)) {
+    v = mid;
+  } else {
+    const int slots = c.grid_cap > 0 && c.grid_cap < num_cus ? c.grid_cap : num_cus;
+    double best = 0;
+    for (const TileCost &tc : kTileCosts) {
+      const Variant *pv = find_variant(b_kn ? tc.id_kn : tc.id_nk);
+      const double tiles = (double)ceil_div(M, pv->bm) * ceil_div(N, pv->bn);
+      const double rounds = tc.shared ? std::max(1.0, tiles / slots) : std::ceil(tiles / slots);
+      const double t = tc.launch + rounds * (tc.fixed + tc.step * ceil_div(K, 64));
+      if (best == 0 || t < best) {
+        best = t;
+        v = pv->id;
+      }
+    }
+  }
   const Variant *pv = find_variant(v);
-  if (pv->kmax > 0 && K > pv->kmax) {
+  if ((pv->kmax > 0 && K > pv->kmax) || (pv->nmax > 0 && N > pv->nmax)) {
     v = small;
     pv = find_variant(v);
     if (pv->kmax > 0 && K > pv->kmax && !b_kn) v = 7;
@@ -230,7 +313,7 @@ int gemm_launch_plan(const GemmCall &c, occ_gemm_plan *plan) {
   int st = current_device_info(&di);
   if (st != OCC_OK) return st;
   int variant = c.variant;
-  if (variant == 0) variant = auto_variant(c.M, c.N, c.K, di->num_cus, c.b_kn);
+  if (variant == 0) variant = auto_variant(c, di->num_cus);
   return fill_plan(c, variant, *di, plan);
 }
 
@@ -262,16 +345,19 @@ int gemm_launch(const GemmCall &c, hipStream_t s) {
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return OCC_ENODEV;
   if (v->fn) {
     int dyn = v->lds + (int)c.lds_bytes;
-    static bool attr_set[kMaxDevices][kMaxVariantId + 1] = {};
-    if (!attr_set[dev][v->id]) {
-      if (hipFuncSetAttribute(reinterpret_cast<const void *>(v->fn),
+    int tiles_m = ceil_div(c.M, v->bm), tiles_n = ceil_div(c.N, v->bn);
+    // B read by one workgroup only and too large to stay cached: non-temporal
+    const bool nt = v->fn_nt != nullptr && tiles_m == 1 && b_exceeds_llc(c.N, c.K);
+    const TiledFn fn = nt ? v->fn_nt : v->fn;
+    static bool attr_set[kMaxDevices][kMaxVariantId + 1][2] = {};
+    if (!attr_set[dev][v->id][nt]) {
+      if (hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
                               hipFuncAttributeMaxDynamicSharedMemorySize,
                               p.max_lds_per_wg) != hipSuccess)
         return OCC_EHIP;
-      attr_set[dev][v->id] = true;
+      attr_set[dev][v->id][nt] = true;
     }
-    int tiles_m = ceil_div(c.M, v->bm), tiles_n = ceil_div(c.N, v->bn);
-    hipLaunchKernelGGL(v->fn, dim3(p.grid), dim3(v->threads), dyn, s, A, B, C, c.M, c.N, c.K,
+    hipLaunchKernelGGL(fn, dim3(p.grid), dim3(v->threads), dyn, s, A, B, C, c.M, c.N, c.K,
                        tiles_m, tiles_n, c.priority, c.trace);
   } else {
     static bool attr_set_skinny[kMaxDevices][kMaxVariantId + 1] = {};

@@ -4,6 +4,8 @@
 #include "device_util.h"
 #include "occ_internal.h"
 
+#include <type_traits>
+
 namespace occ {
 namespace {
 
@@ -20,16 +22,23 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   return (uint32_t)to_bf16(lo) | ((uint32_t)to_bf16(hi) << 16);
 }
 
-// Stores of C, non-temporal (written once and not read again by the kernel).
-// `through`: at device scope, i.e. through the XCD's L2 to memory, so that a
+// Stores of C.  THROUGH / `through`: at device scope, i.e. through the XCD's L2 to memory, so that a
 // store that has completed is visible to the whole device (the hooks'
 // release, see hooks_end).
-__device__ __forceinline__ void store_c(uint16_t *p, uint16_t v, bool through) {
-  if (through) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// Non-temporal otherwise: C is written once and not read again by the kernel.
+template <bool THROUGH>
+__device__ __forceinline__ void store_c(uint16_t *p, uint16_t v) {
+  if constexpr (THROUGH) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   else __builtin_nontemporal_store(v, p);
 }
+// The skinny and register-staged kernels' stores, through the L2's usual policy
+// otherwise: non-temporal ones of their short runs cost 2 % on 16x28672x8192.
+__device__ __forceinline__ void store_c_cached(uint16_t *p, uint16_t v, bool through) {
+  if (__builtin_expect(through, 0)) store_c<true>(p, v);
+  else *p = v;
+}
 
-// The same, 16 bytes at a byte offset (below 2^32, a multiple of 16) of `base`;
+// The same, non-temporal, 16 bytes at a byte offset (below 2^32, a multiple of 16) of `base`;
 // offsets at or past `bytes` store nothing.  base and bytes are wave-uniform.
 struct CStore {
   __amdgpu_buffer_rsrc_t rsrc;
@@ -42,6 +51,25 @@ struct CStore {
     else __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)off, 0, kNt);
   }
 };
+
+// 8 columns of a row of C whose rows are not 16-byte aligned (N not a multiple of
+// 8): one 2-byte-aligned store where all 8 exist, of the first `left` otherwise.
+// 2-byte stores throughout took 3001x5003x2504 from 78 to 230 us.
+__device__ __forceinline__ void store_c_ragged(uint16_t *p, u32x4 v, int left, bool through) {
+  typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
+  if (left >= 8 && !through) {
+    __builtin_nontemporal_store(v, reinterpret_cast<u32x4_a2 *>(p));
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const uint16_t h = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
+      if (e < left) {
+        if (through) store_c<true>(p + e, h);
+        else store_c<false>(p + e, h);
+      }
+    }
+  }
+}
 
 // ---------------------------------------------------------------------------
 // Tiled kernel.  A workgroup owns a BM x BN output tile; WM x WN waves each

@@ -230,7 +230,7 @@ __global__ __launch_bounds__(T::NT) void gemm_pp_kernel(const uint16_t *__restri
     const int em = el & 15;
     const int en = wn * 32 + ((el >> 4) & 1) * 16 + (el >> 5) * 8;
     // 16-byte stores when the rows of C are 16-byte aligned (and, for the
-    // 32-bit offsets of 16 rows, N within 16 M); else 2-byte stores
+    // 32-bit offsets of 16 rows, N within 16 M)
     const bool wide = (N & 7) == 0 && N <= (1 << 24);
 #pragma unroll
     for (int h = 0; h < 2; ++h)
@@ -254,10 +254,7 @@ __global__ __launch_bounds__(T::NT) void gemm_pp_kernel(const uint16_t *__restri
           if (wide) {
             cs.put(v, n < N ? ((uint32_t)em * (uint32_t)N + (uint32_t)n) * 2u : 0x80000000u);
           } else if (mb + em < M) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-              if (n + e < N)
-                store_c(C + (size_t)(mb + em) * N + n + e, (uint16_t)(v[e >> 1] >> (16 * (e & 1))), tr.release);
+            store_c_ragged(C + (size_t)(mb + em) * N + n, v, N - n, tr.release);
           }
         }
         __builtin_amdgcn_sched_barrier(0);

@@ -96,7 +96,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_skinny_kernel(const uint16_t 
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           int m = 4 * g + i;
-          if (m < M) store_c(&C[(size_t)m * N + n], to_bf16(s[i]), tr.release);
+          if (m < M) store_c_cached(&C[(size_t)m * N + n], to_bf16(s[i]), tr.release);
         }
       }
     }

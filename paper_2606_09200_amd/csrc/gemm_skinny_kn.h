@@ -195,7 +195,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_skinny_kn_kernel(const uint16
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const int m = 4 * grp + i;
-            if (m < M) store_c(&C[(size_t)m * N + n], to_bf16(acc[j][i]), tr.release);
+            if (m < M) store_c_cached(&C[(size_t)m * N + n], to_bf16(acc[j][i]), tr.release);
           }
         }
       }

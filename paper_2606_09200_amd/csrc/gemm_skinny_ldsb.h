@@ -151,7 +151,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_skinny_ldsb_kernel(const uint
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int m = 4 * g + i;
-          if (m < M) store_c(&C[(size_t)m * N + n], to_bf16(sum[i]), tr.release);
+          if (m < M) store_c_cached(&C[(size_t)m * N + n], to_bf16(sum[i]), tr.release);
         }
       }
     }

@@ -140,7 +140,7 @@ __global__ __launch_bounds__(T::NT) void gemm_tiled_kernel(const uint16_t *__res
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             const int m = mb + 8 * (r >> 2) + (r & 3);
-            if (m < M) store_c(&C[(size_t)m * N + n], to_bf16(acc[i][j][r]), tr.release);
+            if (m < M) store_c_cached(&C[(size_t)m * N + n], to_bf16(acc[i][j][r]), tr.release);
           }
         }
       }

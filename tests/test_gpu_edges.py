@@ -125,3 +125,55 @@ def test_permute_alignments(nchunks, chunk_bytes):
         torch.cuda.synchronize()
         assert np.array_equal(view.cpu().numpy(), want), (so, do)
         assert (d[:16 + do] == 77).all() and (d[16 + do + src.numel():] == 77).all(), (so, do)
+
+
+# register-pipelined tiles: one to several k-steps (fewer than, as many as and more
+# than the stages), partial tiles, rows of C off 16 bytes (B N x K); 128x128 with
+# its non-temporal B is covered by the shape rule below
+@pytest.mark.parametrize("layout,variant", [("kn", v) for v in (35, 40, 41, 42)] + [("nk", v) for v in (10, 11, 12, 14)])
+@pytest.mark.parametrize("M,N,K", [(64, 64, 8), (65, 72, 64), (255, 136, 136), (257, 120, 256), (128, 264, 328),
+                                   (40, 129, 520), (130, 67, 1032)])
+def test_register_pipelined_tile_edges(layout, variant, M, N, K):
+    if layout == "kn":
+        N = (N + 7) // 8 * 8
+    for cap in (0, 1):
+        got, ref = int_gemm(M, N, K, layout, variant, cap, seed=M + K)
+        assert np.array_equal(got, ref), cap
+
+
+def test_shape_rule_takes_every_tile_and_gives_the_same_bits():
+    # one shape per tile of the automatic choice; all tiles sum over k in one order
+    for (M, N, K), kn, nk in (((4096, 4096, 512), 32, 16), ((1792, 2816, 1024), 40, 10), ((2048, 2048, 512), 35, 14),
+                              ((1024, 2048, 1024), 41, 11), ((512, 1024, 1536), 42, 12), ((640, 512, 256), 39, 9)):
+        assert occ.occ_gemm_plan_query(M, N, K)["kernel_id"] == kn, (M, N, K)
+        assert occ.occ_gemm_bt_plan_query(M, N, K)["kernel_id"] == nk, (M, N, K)
+        g = torch.Generator(device=DEV).manual_seed(M)
+        A = torch.randn((M, K), generator=g, device=DEV).to(torch.bfloat16)
+        Bt = torch.randn((N, K), generator=g, device=DEV).to(torch.bfloat16)
+        B = Bt.t().contiguous()
+        C = [torch.full((M, N), float("nan"), device=DEV, dtype=torch.bfloat16) for _ in range(3)]
+        occ.occ_gemm(A, B, C[0])
+        occ.occ_gemm_bt(A, Bt, C[1])
+        occ.occ_gemm_ex(A, B, C[2], variant=37)
+        torch.cuda.synchronize()
+        assert torch.equal(C[0].view(torch.int16), C[2].view(torch.int16)), (M, N, K)
+        assert torch.equal(C[1].view(torch.int16), C[2].view(torch.int16)), (M, N, K)
+    # a pad keeps the choice by tile count, and every pad that fitted it
+    assert occ.occ_gemm_plan_query(512, 1024, 1536, 128 << 10)["kernel_id"] == 39
+
+
+@pytest.mark.parametrize("layout", ["kn", "nk"])
+def test_streamed_weight_takes_non_temporal_loads(layout):
+    # B just above the last-level cache, one row of tiles: against the opt2 tile
+    M, N, K = 40, 16520, 8192
+    q = occ.occ_gemm_plan_query if layout == "kn" else occ.occ_gemm_bt_plan_query
+    assert q(M, N, K)["kernel_id"] == (35 if layout == "kn" else 14)
+    g = torch.Generator(device=DEV).manual_seed(5)
+    A = torch.randn((M, K), generator=g, device=DEV).to(torch.bfloat16)
+    B = torch.randn((K, N) if layout == "kn" else (N, K), generator=g, device=DEV).to(torch.bfloat16)
+    C = [torch.full((M, N), float("nan"), device=DEV, dtype=torch.bfloat16) for _ in range(2)]
+    f = occ.occ_gemm_ex if layout == "kn" else occ.occ_gemm_bt_ex
+    f(A, B, C[0])
+    f(A, B, C[1], variant=37 if layout == "kn" else 7)
+    torch.cuda.synchronize()
+    assert torch.equal(C[0].view(torch.int16), C[1].view(torch.int16))
