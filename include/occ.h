@@ -93,6 +93,7 @@ enum {
   OCC_GEMM_RP_256x128x64_8W_3ST = 10,   /* as 40 */
   OCC_GEMM_RP_128x64x64_8W_4ST = 11,    /* as 41 */
   OCC_GEMM_RP_64x64x128_4W_4ST = 12,    /* as 42 */
+  OCC_GEMM_RP_64x128x128_8W_3ST = 13,   /* register-pipelined; default for M <= 64 and a B beyond 256 MB */
   OCC_GEMM_DL_128x128x64_4W_3ST = 14,   /* as 35; default for mid-size shapes */
   OCC_GEMM_DLP_256x256x64_8W_2ST = 16,  /* direct-to-LDS; default for large shapes */
   OCC_GEMM_SKINNY_8W_U8 = 21,           /* M <= 16, any K: 8 waves, 8 k-blocks in flight per lane */

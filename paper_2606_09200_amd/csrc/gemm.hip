@@ -149,6 +149,8 @@ template <bool BKN, bool NTB = false>
 using R128x128 = RpTile<128, 128, 64, 2, 4, 3, 1, BKN, NTB>;
 template <bool BKN>
 using R128x64 = RpTile<128, 64, 64, 4, 2, 4, 2, BKN>;
+template <bool NTB>
+using R64x128k128 = RpTile<64, 128, 128, 2, 4, 3, 2, false, NTB>;
 template <bool BKN>
 using R64x64k128 = RpTile<64, 64, 128, 2, 2, 4, 4, BKN>;
 
@@ -160,6 +162,7 @@ const Variant kVariants[] = {
     make_rp_variant<R256x128<false>>(10, "rp 256x128x64 8w 3st, B N x K"),
     make_rp_variant<R128x64<false>>(11, "rp 128x64x64 8w 4st, B N x K"),
     make_rp_variant<R64x64k128<false>>(12, "rp 64x64x128 4w 4st, B N x K"),
+    make_rp_variant<R64x128k128<false>, R64x128k128<true>>(13, "rp 64x128x128 8w 3st, B N x K"),
     make_rp_variant<R128x128<false>, R128x128<false, true>>(14, "rp 128x128x64 8w 3st, B N x K"),
     make_pp_variant<PpTile<false>>(16, "pp 256x256x64 8w 2st, B N x K"),
     make_skinny_variant<8, 8>(21, "skinny M<=16, 8 waves, unroll 8, B N x K"),
@@ -222,8 +225,11 @@ const TileCost kTileCosts[] = {
 // alone: the largest of 256x256, 128x128 and 64x64 that still gives one
 // 256x256 tile per CU or one 128x128 tile per two CUs.  Without one it is the
 // tile with the least estimated time, except that a B which is read once and
-// comes from memory goes to the 128x128 tile (whose loads can be non-temporal)
-// when that covers M: the tile then matters little, the loads much.  A K or N
+// comes from memory goes to a tile that covers M and whose loads can be
+// non-temporal: the tile then matters little, the loads much.  That is 128x128,
+// or for N x K B and M <= 64 64x128 with k-steps of 128, which read 256-byte
+// pieces of B's rows (64x28672x8192 98 -> 92 us, 64x65536x4096 114 -> 104; K x N
+// B has 256-byte pieces in both and no difference).  A K or N
 // beyond what the chosen tile addresses with 32-bit offsets takes the 64x64
 // tile, and a K beyond that (B N x K) the register-staged opt2 tile.
 int auto_variant(const GemmCall &c, int num_cus) {
@@ -243,7 +249,7 @@ int auto_variant(const GemmCall &c, int num_cus) {
     long long mids = (long long)ceil_div(M, 128) * ceil_div(N, 128);
     v = big >= num_cus ? large : (mids >= num_cus / 2 ? mid : small);
   } else if (M <= 128 && b_exceeds_llc(N, K)) {
-    v = mid;
+    v = !b_kn && M <= 64 ? 13 : mid;
   } else {
     const int slots = c.grid_cap > 0 && c.grid_cap < num_cus ? c.grid_cap : num_cus;
     double best = 0;

@@ -130,7 +130,7 @@ def test_permute_alignments(nchunks, chunk_bytes):
 # register-pipelined tiles: one to several k-steps (fewer than, as many as and more
 # than the stages), partial tiles, rows of C off 16 bytes (B N x K); 128x128 with
 # its non-temporal B is covered by the shape rule below
-@pytest.mark.parametrize("layout,variant", [("kn", v) for v in (35, 40, 41, 42)] + [("nk", v) for v in (10, 11, 12, 14)])
+@pytest.mark.parametrize("layout,variant", [("kn", v) for v in (35, 40, 41, 42)] + [("nk", v) for v in (10, 11, 12, 13, 14)])
 @pytest.mark.parametrize("M,N,K", [(64, 64, 8), (65, 72, 64), (255, 136, 136), (257, 120, 256), (128, 264, 328),
                                    (40, 129, 520), (130, 67, 1032)])
 def test_register_pipelined_tile_edges(layout, variant, M, N, K):
@@ -162,12 +162,12 @@ def test_shape_rule_takes_every_tile_and_gives_the_same_bits():
     assert occ.occ_gemm_plan_query(512, 1024, 1536, 128 << 10)["kernel_id"] == 39
 
 
-@pytest.mark.parametrize("layout", ["kn", "nk"])
-def test_streamed_weight_takes_non_temporal_loads(layout):
+@pytest.mark.parametrize("layout,M,kernel", [("kn", 40, 35), ("nk", 40, 13), ("nk", 70, 14)])
+def test_streamed_weight_takes_non_temporal_loads(layout, M, kernel):
     # B just above the last-level cache, one row of tiles: against the opt2 tile
-    M, N, K = 40, 16520, 8192
+    N, K = 16520, 8192
     q = occ.occ_gemm_plan_query if layout == "kn" else occ.occ_gemm_bt_plan_query
-    assert q(M, N, K)["kernel_id"] == (35 if layout == "kn" else 14)
+    assert q(M, N, K)["kernel_id"] == kernel
     g = torch.Generator(device=DEV).manual_seed(5)
     A = torch.randn((M, K), generator=g, device=DEV).to(torch.bfloat16)
     B = torch.randn((K, N) if layout == "kn" else (N, K), generator=g, device=DEV).to(torch.bfloat16)
