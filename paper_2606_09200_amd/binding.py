@@ -149,8 +149,9 @@ def _check(status, where):
 
 def _stream(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        # the current stream's handle alone: building torch's Stream object takes 2.5 us of an 8 us call
+        return _P(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    return _P(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
 
 
 def _ptr(t):
@@ -228,8 +229,19 @@ def occ_gemm_info():
     return tuple(x.value for x in v)
 
 
+def _row_ptrs(t):
+    """Pointers of the rows of a float32 GPU tensor with contiguous rows, else None."""
+    if t.dim() != 2 or t.dtype != torch.float32 or not t.is_cuda or t.numel() == 0 or t.stride(1) != 1:
+        return None
+    n, base, step = t.shape[0], t.data_ptr(), 4 * t.stride(0)
+    return (_P * n)(*range(base, base + n * step, step)) if step > 0 else None
+
+
 def _chunk_ptrs(bufs):
     if isinstance(bufs, torch.Tensor):
+        arr = _row_ptrs(bufs)
+        if arr is not None:
+            return arr, bufs.shape[0], bufs.shape[1]
         bufs = list(bufs.unbind(0)) if bufs.dim() == 2 else [bufs]
     for b in bufs:
         if b.dtype != torch.float32 or not b.is_cuda or not b.is_contiguous():
@@ -259,6 +271,9 @@ def _peer_ptrs(peers, length):
     if peers is None:
         peers = []
     elif isinstance(peers, torch.Tensor):
+        arr = _row_ptrs(peers) if peers.dim() == 2 and peers.shape[1] == length else None
+        if arr is not None:
+            return arr, peers.shape[0]
         peers = list(peers.unbind(0)) if peers.dim() == 2 else [peers]
     for b in peers:
         if b.dtype != torch.float32 or not b.is_cuda or not b.is_contiguous() or b.numel() != length:
@@ -281,6 +296,10 @@ def share_reduce_own(own, peers, out, stream=None, wgs=0, priority=0):
 
 
 def _perm_arr(perm):
+    if isinstance(perm, torch.Tensor) and perm.dtype == torch.int32 and perm.dim() == 1 and not perm.is_cuda \
+            and perm.is_contiguous() and perm.numel() > 0:
+        # read in place; the caller holds the tensor until the call returns
+        return (ctypes.c_int32 * perm.numel()).from_address(perm.data_ptr()), perm.numel()
     p = [int(x) for x in (perm.tolist() if hasattr(perm, "tolist") else perm)]
     return (ctypes.c_int32 * max(1, len(p)))(*p), len(p)
 
