@@ -51,6 +51,10 @@ struct Variant {
   int nmax;          // largest N the kernel takes (0 = any)
   int per_cu;        // skinny kernels: persistent workgroups per CU (0 = 1)
   TiledFn fn_nt;     // the same with B's loads non-temporal, where the kernel has that form
+  // the same with C's stores of device scope, where that is a kernel of its own
+  // (the others choose at run time)
+  TiledFn fn_through = nullptr;
+  SkinnyFn skinny_through = nullptr;
 };
 
 template <class T>
@@ -76,8 +80,8 @@ constexpr int dl_nmax() {
 
 template <class T>
 constexpr Variant make_dl_variant(int id, const char *name) {
-  return Variant{id, T::BM, T::BN, T::BK, T::NT, T::LDS_BYTES, gemm_dl_kernel<T>, nullptr, name,
-                 dl_kmax<T>(), 0, T::BKN, dl_nmax<T>(), 0, nullptr};
+  return Variant{id, T::BM, T::BN, T::BK, T::NT, T::LDS_BYTES, gemm_dl_kernel<T, false>, nullptr, name,
+                 dl_kmax<T>(), 0, T::BKN, dl_nmax<T>(), 0, nullptr, gemm_dl_kernel<T, true>};
 }
 
 // The two-group kernel addresses its operands in the same way.
@@ -112,8 +116,9 @@ constexpr Variant make_skinny_variant(int id, const char *name) {
 template <int WAVES, int STAGES, int COLS>
 constexpr Variant make_skinny_kn_variant(int id, const char *name) {
   return Variant{id, 16, COLS, kSknKB, 64 * WAVES, SkinnyKn<WAVES, STAGES, COLS>::LDS_BYTES, nullptr,
-                 gemm_skinny_kn_kernel<WAVES, STAGES, COLS>, name, (int)((0x80000000ull / 32u) & ~7ull), 0,
-                 true, (int)((0x80000000ull / (2u * kSknKB)) & ~7ull), 2, nullptr};
+                 gemm_skinny_kn_kernel<WAVES, STAGES, COLS, false>, name, (int)((0x80000000ull / 32u) & ~7ull), 0,
+                 true, (int)((0x80000000ull / (2u * kSknKB)) & ~7ull), 2, nullptr, nullptr,
+                 gemm_skinny_kn_kernel<WAVES, STAGES, COLS, true>};
 }
 
 // B staged through LDS in 128-k blocks, A in registers: K a multiple of
@@ -121,8 +126,8 @@ constexpr Variant make_skinny_kn_variant(int id, const char *name) {
 template <int WAVES, int STAGES, int KBW>
 constexpr Variant make_skinny_ldsb_variant(int id, const char *name) {
   return Variant{id, 16, 16, kSlbKB, 64 * WAVES, SkinnyLdsB<WAVES, STAGES, KBW>::LDS_BYTES, nullptr,
-                 gemm_skinny_ldsb_kernel<WAVES, STAGES, KBW>, name, 32 * WAVES * KBW, kSlbKB * WAVES, false, 0, 1,
-                 nullptr};
+                 gemm_skinny_ldsb_kernel<WAVES, STAGES, KBW, false>, name, 32 * WAVES * KBW, kSlbKB * WAVES, false, 0, 1,
+                 nullptr, nullptr, gemm_skinny_ldsb_kernel<WAVES, STAGES, KBW, true>};
 }
 
 // B stored N x K (occ_gemm_bt)
@@ -181,6 +186,10 @@ const Variant kVariants[] = {
     make_rp_variant<R64x64k128<true>>(42, "rp 64x64x128 4w 4st, B K x N"),
 };
 
+// Variant 33's narrower units (gemm_skinny_kn.h); same sums, bit for bit.
+const Variant kSkinnyKn64 = make_skinny_kn_variant<4, 3, 64>(33, "skinny M<=16, 64-column units, 4 waves, 3 LDS stages, B K x N");
+const Variant kSkinnyKn32 = make_skinny_kn_variant<4, 4, 32>(33, "skinny M<=16, 32-column units, 4 waves, 4 LDS stages, B K x N");
+
 constexpr int kMaxVariantId = 63;  // launch-attribute caches are indexed by id
 constexpr int kMaxDevices = 64;    // and by device
 
@@ -193,6 +202,17 @@ const Variant *find_variant(int id) {
 }
 
 int ceil_div(long long a, long long b) { return (int)((a + b - 1) / b); }
+
+// The form of variant `id` for a call: variant 33 takes the widest units that
+// leave no CU without one, down to a quarter of the CUs with 32 columns.  With
+// a pad it keeps the 128-column units, whose LDS the pad is meant to add to.
+const Variant *variant_form(const GemmCall &c, int id, int num_cus) {
+  if (id == 33 && c.lds_bytes == 0) {
+    if (ceil_div(c.N, 32) <= num_cus / 4) return &kSkinnyKn32;
+    if (ceil_div(c.N, 64) <= num_cus) return &kSkinnyKn64;
+  }
+  return find_variant(id);
+}
 
 // B too large for the 256 MB last-level cache.
 bool b_exceeds_llc(int N, int K) { return (long long)N * K * 2 > (256ll << 20); }
@@ -281,7 +301,7 @@ bool gemm_variant_is_kn(int id) {
 }
 
 static int fill_plan(const GemmCall &c, int variant, const DeviceInfo &di, occ_gemm_plan *p) {
-  const Variant *v = find_variant(variant);
+  const Variant *v = variant_form(c, variant, di.num_cus);
   if (v == nullptr) return OCC_EINVAL;
   const bool skinny = is_skinny(v);
   if (skinny && c.M > 16) return OCC_EINVAL;
@@ -326,7 +346,7 @@ int gemm_launch_plan(const GemmCall &c, occ_gemm_plan *plan) {
 int gemm_plan(const GemmCall &c, occ_gemm_plan *plan) {
   int st = gemm_launch_plan(c, plan);
   if (st != OCC_OK) return st;
-  const Variant *v = find_variant(plan->kernel_id);
+  const Variant *v = variant_form(c, plan->kernel_id, plan->num_cus);
   int dyn = (int)(v->fn ? v->lds + c.lds_bytes : c.lds_bytes);
   int nb = 0;
   hipError_t e = v->fn ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, v->fn, v->threads, dyn)
@@ -341,7 +361,7 @@ int gemm_launch(const GemmCall &c, hipStream_t s) {
   int st = gemm_launch_plan(c, &p);
   if (st != OCC_OK) return st;
   if (c.M == 0 || c.N == 0) return OCC_OK;
-  const Variant *v = find_variant(p.kernel_id);
+  const Variant *v = variant_form(c, p.kernel_id, p.num_cus);
   const uint16_t *A = static_cast<const uint16_t *>(c.A);
   const uint16_t *B = static_cast<const uint16_t *>(c.B);
   uint16_t *C = static_cast<uint16_t *>(c.C);
@@ -354,28 +374,32 @@ int gemm_launch(const GemmCall &c, hipStream_t s) {
     int tiles_m = ceil_div(c.M, v->bm), tiles_n = ceil_div(c.N, v->bn);
     // B read by one workgroup only and too large to stay cached: non-temporal
     const bool nt = v->fn_nt != nullptr && tiles_m == 1 && b_exceeds_llc(c.N, c.K);
-    const TiledFn fn = nt ? v->fn_nt : v->fn;
+    const bool through = c.trace.release && v->fn_through != nullptr;
+    const TiledFn fn = nt ? v->fn_nt : through ? v->fn_through : v->fn;
     static bool attr_set[kMaxDevices][kMaxVariantId + 1][2] = {};
-    if (!attr_set[dev][v->id][nt]) {
+    const int form = nt || through;  // a variant has at most one of the two
+    if (!attr_set[dev][v->id][form]) {
       if (hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
                               hipFuncAttributeMaxDynamicSharedMemorySize,
                               p.max_lds_per_wg) != hipSuccess)
         return OCC_EHIP;
-      attr_set[dev][v->id][nt] = true;
+      attr_set[dev][v->id][form] = true;
     }
     hipLaunchKernelGGL(fn, dim3(p.grid), dim3(v->threads), dyn, s, A, B, C, c.M, c.N, c.K,
                        tiles_m, tiles_n, c.priority, c.trace);
   } else {
-    static bool attr_set_skinny[kMaxDevices][kMaxVariantId + 1] = {};
-    if (!attr_set_skinny[dev][v->id]) {
-      if (hipFuncSetAttribute(reinterpret_cast<const void *>(v->skinny),
-                              hipFuncAttributeMaxDynamicSharedMemorySize,
+    // the attribute matters to pads only, and with a pad a variant has one width
+    const bool through = c.trace.release && v->skinny_through != nullptr;
+    const SkinnyFn fn = through ? v->skinny_through : v->skinny;
+    static bool attr_set_skinny[kMaxDevices][kMaxVariantId + 1][2] = {};
+    if (c.lds_bytes > 0 && !attr_set_skinny[dev][v->id][through]) {
+      if (hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
                               p.max_lds_per_wg - v->lds) != hipSuccess)
         return OCC_EHIP;
-      attr_set_skinny[dev][v->id] = true;
+      attr_set_skinny[dev][v->id][through] = true;
     }
-    hipLaunchKernelGGL(v->skinny, dim3(p.grid), dim3(v->threads), (int)c.lds_bytes, s, A, B, C,
-                       c.M, c.N, c.K, c.priority, c.trace);
+    hipLaunchKernelGGL(fn, dim3(p.grid), dim3(v->threads), (int)c.lds_bytes, s, A, B, C, c.M, c.N, c.K,
+                       c.priority, c.trace);
   }
   return hipGetLastError() == hipSuccess ? OCC_OK : OCC_EHIP;
 }

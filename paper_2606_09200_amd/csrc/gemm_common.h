@@ -22,7 +22,8 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   return (uint32_t)to_bf16(lo) | ((uint32_t)to_bf16(hi) << 16);
 }
 
-// Stores of C.  THROUGH / `through`: at device scope, i.e. through the XCD's L2 to memory, so that a
+// Stores of C.  THROUGH / `through` (chosen once per tile, not per store: a branch at
+// each 2-byte store cost 1 us of 14): at device scope, i.e. through the XCD's L2 to memory, so that a
 // store that has completed is visible to the whole device (the hooks'
 // release, see hooks_end).
 // Non-temporal otherwise: C is written once and not read again by the kernel.
@@ -33,8 +34,9 @@ __device__ __forceinline__ void store_c(uint16_t *p, uint16_t v) {
 }
 // The skinny and register-staged kernels' stores, through the L2's usual policy
 // otherwise: non-temporal ones of their short runs cost 2 % on 16x28672x8192.
-__device__ __forceinline__ void store_c_cached(uint16_t *p, uint16_t v, bool through) {
-  if (__builtin_expect(through, 0)) store_c<true>(p, v);
+template <bool THROUGH>
+__device__ __forceinline__ void store_c_cached(uint16_t *p, uint16_t v) {
+  if constexpr (THROUGH) store_c<true>(p, v);
   else *p = v;
 }
 

@@ -62,7 +62,9 @@ __device__ __forceinline__ void wait_stages(int ahead) {
   }
 }
 
-template <class T>
+// THROUGH: C's stores are of device scope (KHooks::release).  A kernel of its own,
+// because even a branch once per tile shows in the smallest launches.
+template <class T, bool THROUGH>
 __global__ __launch_bounds__(T::NT, T::MINB) void gemm_dl_kernel(const uint16_t *__restrict__ A,
                                                         const uint16_t *__restrict__ B,
                                                         uint16_t *__restrict__ C, int M, int N,
@@ -247,28 +249,24 @@ __global__ __launch_bounds__(T::NT, T::MINB) void gemm_dl_kernel(const uint16_t 
     // stores keep it from displacing operand lines in the caches (≈ 1 % on
     // 8192^3)
     const int ncol = lane & 31;
-    auto store_tile = [&](auto through) {
 #pragma unroll
-      for (int i = 0; i < T::FM; ++i) {
+    for (int i = 0; i < T::FM; ++i) {
 #pragma unroll
-        for (int j = 0; j < T::FN; ++j) {
-          const int n = n0 + wn * T::TN + j * 32 + ncol;
-          const int mb = m0 + wm * T::TM + i * 32 + 4 * half;
-          if (n < N) {
+      for (int j = 0; j < T::FN; ++j) {
+        const int n = n0 + wn * T::TN + j * 32 + ncol;
+        const int mb = m0 + wm * T::TM + i * 32 + 4 * half;
+        if (n < N) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const int m = mb + 8 * (r >> 2) + (r & 3);
-              if (m < M) store_c<decltype(through)::value>(&C[(size_t)m * N + n], to_bf16(acc[i][j][r]));
-            }
+          for (int r = 0; r < 16; ++r) {
+            const int m = mb + 8 * (r >> 2) + (r & 3);
+            if (m < M) store_c<THROUGH>(&C[(size_t)m * N + n], to_bf16(acc[i][j][r]));
           }
-          // keep the accumulator reads of one block next to its stores (the
-          // scheduler would otherwise hoist all of them and exhaust registers)
-          __builtin_amdgcn_sched_barrier(0);
         }
+        // keep the accumulator reads of one block next to its stores (the
+        // scheduler would otherwise hoist all of them and exhaust registers)
+        __builtin_amdgcn_sched_barrier(0);
       }
-    };
-    if (__builtin_expect(tr.release, 0)) store_tile(std::true_type{});
-    else store_tile(std::false_type{});
+    }
   }
   hooks_end(tr, t0);
 }

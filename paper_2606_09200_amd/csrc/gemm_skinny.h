@@ -11,8 +11,10 @@ namespace {
 // 16 output columns (16 rows of B) over the whole K.  Persistent workgroups
 // (one per CU by default) loop over units; the 4 waves of a workgroup split
 // K in quarters and stream their share of the 16 B rows straight from HBM
-// into 16x16x32 MFMA operands (non-temporal: every B element is used once),
-// UNROLL 32-wide k-blocks of loads in flight per lane.  In a 32-wide k-block
+// into 16x16x32 MFMA operands, UNROLL 32-wide k-blocks of loads in flight per
+// lane.  A load reads 64-byte pieces, half a cache line, whose other half the
+// next k-block reads: with the default policy the L2 still has it (16x28672x4000
+// 73 us; non-temporal 84).  In a 32-wide k-block
 // lane l feeds row l % 16 and k-group l / 16, so one load instruction reads a
 // contiguous 64-byte run of each of 16 rows.  A (16 x K, L2-resident) is read
 // the same way.  The four partial 16x16 sums are added in wave order
@@ -52,7 +54,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_skinny_kernel(const uint16_t 
       for (int u = 0; u < kSkinnyUnroll; ++u) {
         const int k = (b + u) * kSkinnyKB + g * 8;
         u32x4 zb = {0u, 0u, 0u, 0u};
-        if (brow_ok && k < K) zb = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(brow + k));
+        if (brow_ok && k < K) zb = *reinterpret_cast<const u32x4 *>(brow + k);
         bv[u] = zb;
       }
 #pragma unroll
@@ -72,7 +74,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_skinny_kernel(const uint16_t 
       u32x4 za = {0u, 0u, 0u, 0u}, zb = {0u, 0u, 0u, 0u};
       if (k < K) {
         if (arow_ok) za = *reinterpret_cast<const u32x4 *>(arow + k);
-        if (brow_ok) zb = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(brow + k));
+        if (brow_ok) zb = *reinterpret_cast<const u32x4 *>(brow + k);
       }
       acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, za),
                                                     __builtin_bit_cast(bf16x8, zb), acc, 0, 0, 0);
@@ -92,13 +94,17 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_skinny_kernel(const uint16_t 
       }
       // 16x16 MFMA result layout: lane holds column (lane % 16), rows 4*(lane/16) + i.
       const int n = n0 + r;
-      if (n < N) {
+      auto store_unit = [&](auto through) {
+        if (n < N) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          int m = 4 * g + i;
-          if (m < M) store_c_cached(&C[(size_t)m * N + n], to_bf16(s[i]), tr.release);
+          for (int i = 0; i < 4; ++i) {
+            int m = 4 * g + i;
+            if (m < M) store_c_cached<decltype(through)::value>(&C[(size_t)m * N + n], to_bf16(s[i]));
+          }
         }
-      }
+      };
+      if (__builtin_expect(tr.release, 0)) store_unit(std::true_type{});
+      else store_unit(std::false_type{});
     }
     __syncthreads();  // partial[] is reused by the next unit
   }

@@ -18,9 +18,20 @@ namespace {
 //   block buffer = [A: 16 rows x 64 B][B: 32 rows x 2*COLS B]
 //
 // A (16 x K, L2-resident) comes through the same DMA, so one counter orders
-// both; B's DMA is non-temporal (every B byte is used once).  Measured on
-// 16 x 28672 x 8192: 256-byte row pieces stream 15-20 % faster than
-// 128-byte ones, and the non-temporal policy adds 7-8 %.  MFMA
+// both.  Measured on 16 x 28672 x 8192: 256-byte row pieces stream 15-20 %
+// faster than 128-byte ones, and the non-temporal policy adds 7-8 %.
+//
+// With few columns the time is that of one workgroup's rows, 5-7 ns each
+// whatever is in flight, so narrower units on more CUs win as long as they take
+// one round: 64 columns up to one unit per CU, 32 up to a quarter of that (the K
+// split and the order of the sums are the same).  Their pieces are read with the
+// default policy: from memory it costs nothing there, and a B that the
+// last-level cache still holds takes a third less time.  us per launch, B from
+// memory / from that cache, before -> now: 14x1248x7080 52 / 47 -> 25 / 16.5;
+// 16x4096x4096 30 / 28.5 -> 23.5 / 13.4; 16x8192x8192 57 / 56 -> 45 / 25;
+// 16x14336x4096 39 / 37 -> 28 / 22; 16x16384x8192 65 / 65 -> 57 / 43.  (With 128
+// columns the default policy saves 20 % on a cached B and costs 4-6 % on one
+// from memory.)  MFMA
 // v_mfma_f32_16x16x32_bf16, one per 16-column block per k-block: the A
 // operand (lane: row l % 16, k-group l / 16) is a 16-byte LDS read; the B
 // operand (lane: column l % 16, 8 consecutive k of k-group l / 16) is two LDS
@@ -38,11 +49,13 @@ constexpr int kSknABytes = 16 * kSknKB * 2;  // A part of a block buffer: 1 KiB
 // are ROW_BYTES long.  A transpose read touches, per 32 lanes, 8 rows (r..r+3
 // and r+8..r+11) at one 32-byte column piece each; the XOR moves those 8
 // pieces to 8 different 32-byte slots of the 256-byte bank line (128-byte
-// rows: two rows share a line, so each parity class needs 4 slots).
+// rows: two rows share a line, so each parity class needs 4 slots; 64-byte
+// rows: four share a line, and only rows r and r+8 collide).
 template <int ROW_BYTES>
 __device__ __forceinline__ int swz_skn_b(int r, int c) {
   if constexpr (ROW_BYTES == 256) return c ^ (2 * ((r & 3) | (((r >> 3) & 1) << 2)));
-  else return c ^ (2 * (((r >> 1) & 1) | (((r >> 3) & 1) << 1)));
+  else if constexpr (ROW_BYTES == 128) return c ^ (2 * (((r >> 1) & 1) | (((r >> 3) & 1) << 1)));
+  else return c ^ (2 * ((r >> 3) & 1));
 }
 
 // Physical chunk of logical chunk g (8 k) in A row m: an operand read sends
@@ -72,12 +85,14 @@ struct SkinnyKn {
   static constexpr int NB16 = COLS / 16;                   // 16-column MFMA blocks
   static constexpr int WAVE_BYTES = STAGES * BLOCK_BYTES;
   static constexpr int LDS_BYTES = WAVES * WAVE_BYTES;
-  static_assert(COLS == 64 || COLS == 128, "unit of 64 or 128 columns");
+  static constexpr bool NTB = COLS == 128;                 // B's DMA is non-temporal
+  static_assert(COLS == 32 || COLS == 64 || COLS == 128, "unit of 32, 64 or 128 columns");
   static_assert(WAVE_BYTES >= NB16 * 64 * 16, "a wave's partial sums must fit its ring");
   static_assert(STAGES >= 2 && (STAGES - 1) * LOADS <= 63, "vmcnt holds at most 63");
 };
 
-template <int WAVES, int STAGES, int COLS>
+// THROUGH: C's stores are of device scope (KHooks::release).
+template <int WAVES, int STAGES, int COLS, bool THROUGH>
 __global__ __launch_bounds__(64 * WAVES) void gemm_skinny_kn_kernel(const uint16_t *__restrict__ A,
                                                                     const uint16_t *__restrict__ B,
                                                                     uint16_t *__restrict__ C, int M,
@@ -139,7 +154,10 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_skinny_kn_kernel(const uint16
       const int have = min(kSknKB, K - k0);
       const i32x4 rsrc_b = make_rsrc(B + (size_t)k0 * N + n0, (uint32_t)have * (uint32_t)N * 2u - (uint32_t)n0 * 2u);
 #pragma unroll
-      for (int q = 0; q < G::B_LOADS; ++q) lds_dma16_nt(rsrc_b, slot + (uint32_t)(kSknABytes + q * 1024), vb[q]);
+      for (int q = 0; q < G::B_LOADS; ++q) {
+        if constexpr (G::NTB) lds_dma16_nt(rsrc_b, slot + (uint32_t)(kSknABytes + q * 1024), vb[q]);
+        else lds_dma16(rsrc_b, slot + (uint32_t)(kSknABytes + q * 1024), vb[q]);
+      }
     };
 
     f32x4 acc[G::NB16];
@@ -195,7 +213,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_skinny_kn_kernel(const uint16
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const int m = 4 * grp + i;
-            if (m < M) store_c_cached(&C[(size_t)m * N + n], to_bf16(acc[j][i]), tr.release);
+            if (m < M) store_c_cached<THROUGH>(&C[(size_t)m * N + n], to_bf16(acc[j][i]));
           }
         }
       }

@@ -130,21 +130,25 @@ __global__ __launch_bounds__(T::NT) void gemm_tiled_kernel(const uint16_t *__res
     // Epilogue.  32x32 MFMA result layout: lane holds column (lane % 32) and
     // rows 8*(r/4) + 4*(lane/32) + r%4 of the block, r = 0..15.
     const int ncol = lane & 31;
+    auto store_tile = [&](auto through) {
 #pragma unroll
-    for (int i = 0; i < T::FM; ++i) {
+      for (int i = 0; i < T::FM; ++i) {
 #pragma unroll
-      for (int j = 0; j < T::FN; ++j) {
-        const int n = n0 + wn * T::TN + j * 32 + ncol;
-        const int mb = m0 + wm * T::TM + i * 32 + 4 * half;
-        if (n < N) {
+        for (int j = 0; j < T::FN; ++j) {
+          const int n = n0 + wn * T::TN + j * 32 + ncol;
+          const int mb = m0 + wm * T::TM + i * 32 + 4 * half;
+          if (n < N) {
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int m = mb + 8 * (r >> 2) + (r & 3);
-            if (m < M) store_c_cached(&C[(size_t)m * N + n], to_bf16(acc[i][j][r]), tr.release);
+            for (int r = 0; r < 16; ++r) {
+              const int m = mb + 8 * (r >> 2) + (r & 3);
+              if (m < M) store_c_cached<decltype(through)::value>(&C[(size_t)m * N + n], to_bf16(acc[i][j][r]));
+            }
           }
         }
       }
-    }
+    };
+    if (__builtin_expect(tr.release, 0)) store_tile(std::true_type{});
+    else store_tile(std::false_type{});
   }
   hooks_end(tr, t0);
 }

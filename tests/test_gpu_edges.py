@@ -177,3 +177,26 @@ def test_streamed_weight_takes_non_temporal_loads(layout, M, kernel):
     f(A, B, C[1], variant=37 if layout == "kn" else 7)
     torch.cuda.synchronize()
     assert torch.equal(C[0].view(torch.int16), C[1].view(torch.int16))
+
+
+# skinny K x N: 32-, 64- and 128-column units at and around their limits, the
+# widest with a pad for every N, K of less than a block per wave and ragged
+@pytest.mark.parametrize("M,N,K", [(1, 8, 8), (5, 40, 72), (16, 2048, 200), (13, 2056, 136), (16, 2120, 1032),
+                                   (7, 16384, 40), (16, 16392, 64)])
+def test_skinny_kn_unit_widths(M, N, K):
+    cus = occ.occ_gemm_plan_query(512, 512, 512)["num_cus"]
+    plan = occ.occ_gemm_plan_query(M, N, K)
+    want = 32 if -(-N // 32) <= cus // 4 else 64 if -(-N // 64) <= cus else 128
+    assert plan["kernel_id"] == 33 and plan["tile_n"] == want and plan["tiles"] == -(-N // want)
+    assert occ.occ_gemm_plan_query(M, N, K, 16 << 10)["tile_n"] == 128
+    for cap in (0, 3):
+        got, ref = int_gemm(M, N, K, "kn", 33, cap, seed=N + K)
+        assert np.array_equal(got, ref), cap
+    g = torch.Generator(device=DEV).manual_seed(N)
+    A = torch.randn((M, K), generator=g, device=DEV).to(torch.bfloat16)
+    B = torch.randn((K, N), generator=g, device=DEV).to(torch.bfloat16)
+    C = [torch.full((M, N), float("nan"), device=DEV, dtype=torch.bfloat16) for _ in range(2)]
+    occ.occ_gemm(A, B, C[0])
+    occ.occ_gemm(A, B, C[1], lds_bytes=16 << 10)
+    torch.cuda.synchronize()
+    assert torch.equal(C[0].view(torch.int16), C[1].view(torch.int16))
