@@ -85,6 +85,8 @@ enum {
   OCC_GEMM_KN_256x128x64_8W_3ST = 40,   /* register-pipelined, as the next two; default where a shape */
   OCC_GEMM_KN_128x64x64_8W_4ST = 41,    /*   fills the CUs better with this tile than with the larger */
   OCC_GEMM_KN_64x64x128_4W_4ST = 42,    /*   or smaller ones; the last for small M*N with a long K */
+  OCC_GEMM_KN_32x64x128_4W_3ST = 43,    /* register-pipelined, as the next; defaults where larger tiles */
+  OCC_GEMM_KN_32x32x128_2W_4ST = 44,    /*   would leave half or more of the CUs without one */
   /* B stored N x K (occ_gemm_bt) */
   OCC_GEMM_OPT1_64x64x32 = 6,           /* Table 1 opt1, register-staged, one stage */
   OCC_GEMM_OPT2_64x64x64 = 7,           /* Table 1 opt2, register-staged, one stage; default for a K
@@ -96,6 +98,8 @@ enum {
   OCC_GEMM_RP_64x128x128_8W_3ST = 13,   /* register-pipelined; default for M <= 64 and a B beyond 256 MB */
   OCC_GEMM_DL_128x128x64_4W_3ST = 14,   /* as 35; default for mid-size shapes */
   OCC_GEMM_DLP_256x256x64_8W_2ST = 16,  /* direct-to-LDS; default for large shapes */
+  OCC_GEMM_RP_32x64x128_4W_3ST = 17,    /* as 43 */
+  OCC_GEMM_RP_32x32x128_2W_4ST = 18,    /* as 44 */
   OCC_GEMM_SKINNY_8W_U8 = 21,           /* M <= 16, any K: 8 waves, 8 k-blocks in flight per lane */
   OCC_GEMM_DLP_128x256x32_4W_2ST = 25,  /* two resident workgroups per CU (48 KiB) */
   OCC_GEMM_SKINNY_LDSB_K8192 = 34       /* M <= 16, K a multiple of 1024 up to 8192: A in registers,

@@ -28,11 +28,13 @@ KN_VARIANTS = {
     35: "rp 128x128x64 8w 3st", 36: "opt1 64x64x32 1st", 37: "opt2 64x64x64 1st",
     38: "dl+pipe 128x256x32 4w 2st 2wg/cu", 39: "dl 64x64x64 4w 2st",
     40: "rp 256x128x64 8w 3st", 41: "rp 128x64x64 8w 4st", 42: "rp 64x64x128 4w 4st",
+    43: "rp 32x64x128 4w 3st", 44: "rp 32x32x128 2w 4st",
 }
 NK_VARIANTS = {
     6: "opt1 64x64x32 register-staged", 7: "opt2 64x64x64 register-staged", 9: "dl 64x64x64 4w 2st",
     10: "rp 256x128x64 8w 3st", 11: "rp 128x64x64 8w 4st", 12: "rp 64x64x128 4w 4st",
-    13: "rp 64x128x128 8w 3st", 14: "rp 128x128x64 8w 3st", 16: "pp 256x256x64 8w 2st", 21: "skinny M<=16, 8w, 8 k-blocks in flight",
+    13: "rp 64x128x128 8w 3st", 14: "rp 128x128x64 8w 3st", 16: "pp 256x256x64 8w 2st",
+    17: "rp 32x64x128 4w 3st", 18: "rp 32x32x128 2w 4st", 21: "skinny M<=16, 8w, 8 k-blocks in flight",
     25: "dl+pipe 128x256x32 4w 2st 2wg/cu", 34: "skinny M<=16, A in registers, B through LDS (K%1024==0, K<=8192)",
 }
 SKINNY_VARIANTS = (21, 33, 34)     # M <= 16 only

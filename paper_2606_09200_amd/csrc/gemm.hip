@@ -158,6 +158,10 @@ template <bool NTB>
 using R64x128k128 = RpTile<64, 128, 128, 2, 4, 3, 2, false, NTB>;
 template <bool BKN>
 using R64x64k128 = RpTile<64, 64, 128, 2, 2, 4, 4, BKN>;
+template <bool BKN>
+using R32x64k128 = RpTile<32, 64, 128, 2, 2, 3, 4, BKN>;
+template <bool BKN>
+using R32x32k128 = RpTile<32, 32, 128, 2, 1, 4, 4, BKN>;
 
 const Variant kVariants[] = {
     // B stored N x K
@@ -166,6 +170,8 @@ const Variant kVariants[] = {
     make_dl_variant<D64x64_4w_2s>(9, "dl 64x64x64 4w 2st, B N x K"),
     make_rp_variant<R256x128<false>>(10, "rp 256x128x64 8w 3st, B N x K"),
     make_rp_variant<R128x64<false>>(11, "rp 128x64x64 8w 4st, B N x K"),
+    make_rp_variant<R32x64k128<false>>(17, "rp 32x64x128 4w 3st, B N x K"),
+    make_rp_variant<R32x32k128<false>>(18, "rp 32x32x128 2w 4st, B N x K"),
     make_rp_variant<R64x64k128<false>>(12, "rp 64x64x128 4w 4st, B N x K"),
     make_rp_variant<R64x128k128<false>, R64x128k128<true>>(13, "rp 64x128x128 8w 3st, B N x K"),
     make_rp_variant<R128x128<false>, R128x128<false, true>>(14, "rp 128x128x64 8w 3st, B N x K"),
@@ -184,6 +190,8 @@ const Variant kVariants[] = {
     make_rp_variant<R256x128<true>>(40, "rp 256x128x64 8w 3st, B K x N"),
     make_rp_variant<R128x64<true>>(41, "rp 128x64x64 8w 4st, B K x N"),
     make_rp_variant<R64x64k128<true>>(42, "rp 64x64x128 4w 4st, B K x N"),
+    make_rp_variant<R32x64k128<true>>(43, "rp 32x64x128 4w 3st, B K x N"),
+    make_rp_variant<R32x32k128<true>>(44, "rp 32x32x128 2w 4st, B K x N"),
 };
 
 // Variant 33's narrower units (gemm_skinny_kn.h); same sums, bit for bit.
@@ -225,7 +233,10 @@ bool b_exceeds_llc(int N, int K) { return (long long)N * K * 2 > (256ll << 20); 
 // rounds need not be whole.  On 47 shapes of 64..8192 (M), 128..28672 (N) and
 // 128..8192 (K) in both layouts the choice is within 0.7 % of the fastest tile
 // on average (11 % at most), and 22 % faster than 256x256, 128x128 and 64x64
-// chosen by tile count alone.
+// chosen by tile count alone.  The 32-row tiles win where 64x64 ones leave half
+// of the CUs or more idle: on 39 more shapes of 17..1200 (M), 128..28672 (N) and
+// 520..8192 (K) the choice with them is within 0.5 (N x K) and 0.1 % (K x N) of the
+// fastest on average (19 and 2 % at most).
 struct TileCost {
   int id_nk, id_kn;
   double launch, fixed, step;
@@ -237,6 +248,8 @@ const TileCost kTileCosts[] = {
     {14, 35, 3.0, 2.0, 0.44, false},  // 128x128
     {11, 41, 3.0, 1.6, 0.29, false},  // 128x64
     {12, 42, 3.0, 1.6, 0.19, false},  // 64x64x128
+    {17, 43, 2.5, 1.3, 0.155, false},  // 32x64x128
+    {18, 44, 2.4, 1.2, 0.148, false},  // 32x32x128
     {9, 39, 1.6, 0.4, 0.45, true},    // 64x64
 };
 
@@ -252,6 +265,12 @@ const TileCost kTileCosts[] = {
 // B has 256-byte pieces in both and no difference).  A K or N
 // beyond what the chosen tile addresses with 32-bit offsets takes the 64x64
 // tile, and a K beyond that (B N x K) the register-staged opt2 tile.
+//
+// The 32-row tiles are left to K > kMaxKLaunch.  Up to there a launch is as long
+// as the host needs to enqueue the next (512x512x512: 4.7 us, 3.9 with them, of a
+// call's 6), and a quarter of the workgroups leave the other CUs to a collective;
+// beyond it they pay (20x5552x568 5.3 -> 4.3, 27x1512x1200 6.7 -> 5.4).
+constexpr int kMaxKLaunch = 512;
 int auto_variant(const GemmCall &c, int num_cus) {
   const int M = c.M, N = c.N, K = c.K;
   const bool b_kn = c.b_kn;
@@ -275,6 +294,7 @@ int auto_variant(const GemmCall &c, int num_cus) {
     double best = 0;
     for (const TileCost &tc : kTileCosts) {
       const Variant *pv = find_variant(b_kn ? tc.id_kn : tc.id_nk);
+      if (pv->bm == 32 && K <= kMaxKLaunch) continue;
       const double tiles = (double)ceil_div(M, pv->bm) * ceil_div(N, pv->bn);
       const double rounds = tc.shared ? std::max(1.0, tiles / slots) : std::ceil(tiles / slots);
       const double t = tc.launch + rounds * (tc.fixed + tc.step * ceil_div(K, 64));

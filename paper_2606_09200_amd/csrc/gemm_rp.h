@@ -35,6 +35,14 @@ namespace {
 //   256x128x64, 8 waves, 3 stages: 1707x2792x3488    71 / 74 -> 46 / 46
 //   128x64x64,  8 waves, 4 stages: 1024x2048x4096    39 / 41 -> 22 / 23
 //   64x64x128,  4 waves, 4 stages: 1024x1024x4096    31 / 31 -> 15.5 / 16.5
+// The smaller ones take over where 64x64 tiles are fewer than the CUs; there a
+// k-step costs a wave's ~90 instructions and one LDS round trip, about 600 cycles
+// whatever the tile, so they win by the CUs they add (before = 64x64x128):
+//   32x64x128,  4 waves, 3 stages: 512x1024x4096     14.5 / 16.2 -> 11.7 / 12.1
+//   32x32x128,  2 waves, 4 stages: 292x448x6736      26.1 / 23.5 -> 14.9 / 17.6
+//                                  25x4120x4176      15.1 / 16.9 -> 10.7 / 13.2
+// 32x64 with 5 stages: one workgroup per CU instead of two, the same or slower;
+// 64x32: 10-40 % slower than 32x64 with K x N B; 32x32 with 64-wide k-steps: 25 %.
 // 4 waves with 128x128: 36.6 / 37.2.  More than 3 stages of 128x128 gained
 // nothing; 64-wide k-steps with 6 or 8 stages of 64x64 took 17.
 //
@@ -60,9 +68,10 @@ struct RpTile {
   static constexpr int NG = KS / GS;                // fragment groups per k-step
   static_assert(KS % GS == 0 && (NG == 1 || NG % 2 == 0), "groups alternate between two register sets");
   static_assert(FN % 2 == 0, "16-column blocks are stored in pairs");
-  static_assert(BM % RPP == 0 && RPP % 16 == 0 && (BKN ? BK % B_RPP == 0 && B_RPP % 16 == 0 : BN % RPP == 0),
+  static_assert(BM % RPP == 0 && RPP % 8 == 0 && (BKN ? BK % B_RPP == 0 && B_RPP % 16 == 0 : BN % RPP == 0),
                 "uneven load passes");
-  static_assert(!BKN || BCH == 8 || BCH == 16, "K x N B rows of 64 or 128 columns");
+  static_assert(RPP % 16 == 0 || KCH == 16, "passes of 8 rows: the swizzle of rows 8-15 is that of rows 0-7 with c ^ 8");
+  static_assert(!BKN || BCH == 4 || BCH == 8 || BCH == 16, "K x N B rows of 32, 64 or 128 columns");
   static_assert((STAGES - 1) * LOADS <= 63, "vmcnt holds at most 63");
 };
 
@@ -145,7 +154,9 @@ __global__ __launch_bounds__(T::NT) void gemm_rp_kernel(const uint16_t *__restri
         const bool b = p >= T::A_LOADS;
         const int q = b ? p - T::A_LOADS : p;
         const i32x4 rs = make_rsrc((b ? Bn : Am) + k0, left > 0 ? (b ? b_bytes : a_bytes) - (uint32_t)k0 * 2u : 0u);
-        const uint32_t v = c8 < left ? lane_off : 0x80000000u;
+        // with passes of 8 rows the odd ones are rows 8-15 of 16, whose chunks are swapped by 8 (64 elements)
+        const int c = T::RPP == 8 && (q & 1) ? c8 ^ 64 : c8;
+        const uint32_t v = c < left ? lane_off + (uint32_t)(c - c8) * 2u : 0x80000000u;
         if (b) dma_b(rs, slot + (uint32_t)(T::A_BYTES + q * T::NT * 16), v + (uint32_t)q * pass_step);
         else lds_dma16(rs, slot + (uint32_t)(q * T::NT * 16), v + (uint32_t)q * pass_step);
       }

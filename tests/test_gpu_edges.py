@@ -46,7 +46,7 @@ def test_large_tile_edges(layout, M, N, K):
 @pytest.mark.parametrize("layout,variant,M,N,K", [
     ("kn", 32, 520, 264, 128), ("nk", 16, 520, 264, 128), ("nk", 16, 264, 129, 72), ("kn", 35, 264, 200, 72),
     ("nk", 14, 264, 129, 72), ("kn", 39, 72, 136, 64), ("nk", 9, 72, 133, 64), ("kn", 37, 72, 136, 64),
-    ("nk", 7, 72, 133, 64), ("kn", 33, 16, 264, 136), ("nk", 21, 8, 133, 136), ("nk", 34, 16, 100, 1024)])
+    ("nk", 7, 72, 133, 64), ("kn", 43, 72, 136, 64), ("nk", 18, 72, 133, 64), ("kn", 33, 16, 264, 136), ("nk", 21, 8, 133, 136), ("nk", 34, 16, 100, 1024)])
 def test_collective_reads_the_gemm_output(layout, variant, M, N, K):
     n = 4
     g = torch.Generator().manual_seed(M + N)
@@ -130,9 +130,9 @@ def test_permute_alignments(nchunks, chunk_bytes):
 # register-pipelined tiles: one to several k-steps (fewer than, as many as and more
 # than the stages), partial tiles, rows of C off 16 bytes (B N x K); 128x128 with
 # its non-temporal B is covered by the shape rule below
-@pytest.mark.parametrize("layout,variant", [("kn", v) for v in (35, 40, 41, 42)] + [("nk", v) for v in (10, 11, 12, 13, 14)])
+@pytest.mark.parametrize("layout,variant", [("kn", v) for v in (35, 40, 41, 42, 43, 44)] + [("nk", v) for v in (10, 11, 12, 13, 14, 17, 18)])
 @pytest.mark.parametrize("M,N,K", [(64, 64, 8), (65, 72, 64), (255, 136, 136), (257, 120, 256), (128, 264, 328),
-                                   (40, 129, 520), (130, 67, 1032)])
+                                   (40, 129, 520), (130, 67, 1032), (31, 33, 392)])
 def test_register_pipelined_tile_edges(layout, variant, M, N, K):
     if layout == "kn":
         N = (N + 7) // 8 * 8
@@ -144,7 +144,8 @@ def test_register_pipelined_tile_edges(layout, variant, M, N, K):
 def test_shape_rule_takes_every_tile_and_gives_the_same_bits():
     # one shape per tile of the automatic choice; all tiles sum over k in one order
     for (M, N, K), kn, nk in (((4096, 4096, 512), 32, 16), ((1792, 2816, 1024), 40, 10), ((2048, 2048, 512), 35, 14),
-                              ((1024, 2048, 1024), 41, 11), ((512, 1024, 1536), 42, 12), ((640, 512, 256), 39, 9)):
+                              ((1024, 2048, 1024), 41, 11), ((1024, 1024, 1536), 42, 12), ((640, 512, 256), 39, 9),
+                              ((512, 1024, 1536), 43, 17), ((512, 512, 1536), 44, 18)):
         assert occ.occ_gemm_plan_query(M, N, K)["kernel_id"] == kn, (M, N, K)
         assert occ.occ_gemm_bt_plan_query(M, N, K)["kernel_id"] == nk, (M, N, K)
         g = torch.Generator(device=DEV).manual_seed(M)
