@@ -298,10 +298,13 @@ def share_reduce_own(own, peers, out, stream=None, wgs=0, priority=0):
 
 
 def _perm_arr(perm):
-    if isinstance(perm, torch.Tensor) and perm.dtype == torch.int32 and perm.dim() == 1 and not perm.is_cuda \
-            and perm.is_contiguous() and perm.numel() > 0:
-        # read in place; the caller holds the tensor until the call returns
-        return (ctypes.c_int32 * perm.numel()).from_address(perm.data_ptr()), perm.numel()
+    """Host array of the permutation, always a copy: a schedule reads it at every
+    launch after checking it once, so a later write to the caller's tensor must not reach it."""
+    if isinstance(perm, torch.Tensor) and perm.dtype == torch.int32 and perm.dim() == 1 \
+            and perm.device.type == "cpu" and perm.is_contiguous() and not perm.is_neg() and perm.numel() > 0:
+        arr = (ctypes.c_int32 * perm.numel())()
+        ctypes.memmove(arr, perm.data_ptr(), ctypes.sizeof(arr))
+        return arr, perm.numel()
     p = [int(x) for x in (perm.tolist() if hasattr(perm, "tolist") else perm)]
     return (ctypes.c_int32 * max(1, len(p)))(*p), len(p)
 

@@ -1,6 +1,7 @@
 """The binding's pointer tables against the element-by-element form (CPU)."""
 import ctypes
 
+import pytest
 import torch
 
 from paper_2606_09200_amd import binding as occ
@@ -15,6 +16,23 @@ def test_perm_array_in_place_and_copied_agree():
         assert n == 37 and list(arr)[:n] == base.tolist()
         assert isinstance(arr, ctypes.Array) and arr._type_ is ctypes.c_int32
     assert occ._perm_arr([])[1] == 0 and occ._perm_arr(torch.empty(0, dtype=torch.int32))[1] == 0
+
+
+def test_perm_array_is_a_snapshot():
+    # what the caller writes afterwards (from
+    # another thread, say) cannot reach a launch
+    base = torch.randperm(37).to(torch.int32)
+    want = base.tolist()
+    for f in (base, base.numpy(), torch.cat([base, base])[37:], torch.stack([base, base], 1)[:, 0]):
+        arr, n = occ._perm_arr(f)
+        saved = torch.as_tensor(f).clone()
+        f[...] = 1 << 20
+        assert list(arr)[:n] == want
+        f[...] = saved if isinstance(f, torch.Tensor) else saved.numpy()
+    # a lazily negated view holds other values than its memory
+    assert list(occ._perm_arr(torch._neg_view(-base))[0]) == want
+    with pytest.raises((RuntimeError, NotImplementedError)):
+        occ._perm_arr(torch.empty(4, dtype=torch.int32, device="meta"))
 
 
 def test_row_pointers_only_for_rows_that_can_be_read_as_chunks():
