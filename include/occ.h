@@ -320,7 +320,8 @@ typedef struct occ_overlap_cfg {
   /* bandwidth pacing of the collective in the overlapped schedule, GB/s over
      the whole grid: every comm wave spaces its load/store trips so that the
      kernel streams at no more than this rate, leaving memory bandwidth to the
-     co-running GEMM.  0 = unpaced (full speed); otherwise at least
+     co-running GEMM; the kernel ends no earlier than its bytes take at this
+     rate, however few trips a wave has.  0 = unpaced (full speed); otherwise at least
      OCC_MIN_COMM_RATE_GBS.  The sequential schedule and the isolated kernel
      timings run unpaced, so t_seq stays the fastest sequential makespan,
      unless flags has OCC_RUN_PACE_ALL.  Results are unchanged (same

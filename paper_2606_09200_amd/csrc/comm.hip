@@ -15,6 +15,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 namespace occ {
@@ -97,7 +98,9 @@ __global__ __launch_bounds__(kReduceThreads) void reduce_vec_kernel(ChunkPtrs cp
   Pacer pc = pace_start(pace);
   const I n = (I)nvec;
   const I stride = (I)gridDim.x * kReduceThreads;
-  I i = (I)blockIdx.x * kReduceThreads + threadIdx.x;
+  // the loops below run on the wave's first position, so that the pacing is uniform
+  const I lane = (I)(threadIdx.x & 63);
+  I i0 = (I)blockIdx.x * kReduceThreads + (I)__builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
   auto ld = [&](int c, I k) {
     return __builtin_nontemporal_load(
         reinterpret_cast<const f32x4_a4 *>(reinterpret_cast<const char *>(cp.p[c]) + k * (I)sizeof(f32x4)));
@@ -132,7 +135,7 @@ __global__ __launch_bounds__(kReduceThreads) void reduce_vec_kernel(ChunkPtrs cp
   constexpr int C0 = OWN ? 0 : 1;  // first fp32 chunk added to the first term
 
   if constexpr (NC >= 0) {
-    auto trip = [&](auto positions) {
+    auto trip = [&](auto positions, I i) {
       constexpr int U = decltype(positions)::value;
       f32x4 v[NC > 0 ? NC : 1][U], o[U];
       if constexpr (OWN) {
@@ -151,36 +154,46 @@ __global__ __launch_bounds__(kReduceThreads) void reduce_vec_kernel(ChunkPtrs cp
         st(acc, i + u * stride);
       }
     };
-    for (bool first = true; i + (UNROLL - 1) * stride < n; i += UNROLL * stride, first = false) {
-      if (!first) pace_wait(pc);
-      trip(std::integral_constant<int, UNROLL>{});
-    }
     if constexpr (UNROLL > 1)
-      for (; i < n; i += stride) trip(std::integral_constant<int, 1>{});
+      for (; i0 + 63 + (UNROLL - 1) * stride < n; i0 += UNROLL * stride) {
+        pace_trip(pc);
+        trip(std::integral_constant<int, UNROLL>{}, i0 + lane);
+      }
+    for (; i0 < n; i0 += stride) {
+      pace_trip(pc, 1, UNROLL);
+      if (i0 + lane < n) trip(std::integral_constant<int, 1>{}, i0 + lane);
+    }
   } else {
     // chunk count known at run time: batches of 8 loads, folded in order
-    for (bool first = true; i < n; i += stride, first = false) {
-      if (!first) pace_wait(pc);
-      f32x4 acc = OWN ? ld_own(i) : ld(0, i);
-      for (int c0 = C0; c0 < nchunks; c0 += 8) {
-        f32x4 v[8];
+    for (; i0 < n; i0 += stride) {
+      pace_trip(pc);
+      const I i = i0 + lane;
+      if (i < n) {
+        f32x4 acc = OWN ? ld_own(i) : ld(0, i);
+        for (int c0 = C0; c0 < nchunks; c0 += 8) {
+          f32x4 v[8];
 #pragma unroll
-        for (int c = 0; c < 8; ++c)
-          if (c0 + c < nchunks) v[c] = ld(c0 + c, i);
+          for (int c = 0; c < 8; ++c)
+            if (c0 + c < nchunks) v[c] = ld(c0 + c, i);
 #pragma unroll
-        for (int c = 0; c < 8; ++c)
-          if (c0 + c < nchunks) acc = add(acc, v[c]);
+          for (int c = 0; c < 8; ++c)
+            if (c0 + c < nchunks) acc = add(acc, v[c]);
+        }
+        st(acc, i);
       }
-      st(acc, i);
     }
   }
-  if (blockIdx.x == gridDim.x - 1 && (int)threadIdx.x < head + tail) {
-    const ptrdiff_t j = (int)threadIdx.x < head ? (ptrdiff_t)threadIdx.x - head
-                                                : (ptrdiff_t)(nvec * 4) + (ptrdiff_t)threadIdx.x - head;
-    float acc = OWN ? widen_own(own + j) : cp.p[0][j];
-    for (int c = C0; c < nchunks; ++c) acc = acc + cp.p[c][j];
-    out[j] = acc;
+  if (blockIdx.x == gridDim.x - 1 && head + tail > 0) {
+    pace_trip(pc, 1, UNROLL);
+    if ((int)threadIdx.x < head + tail) {
+      const ptrdiff_t j = (int)threadIdx.x < head ? (ptrdiff_t)threadIdx.x - head
+                                                  : (ptrdiff_t)(nvec * 4) + (ptrdiff_t)threadIdx.x - head;
+      float acc = OWN ? widen_own(own + j) : cp.p[0][j];
+      for (int c = C0; c < nchunks; ++c) acc = acc + cp.p[c][j];
+      out[j] = acc;
+    }
   }
+  pace_end(pc);
   hooks_end(tr, t0);
 }
 
@@ -227,7 +240,7 @@ __global__ __launch_bounds__(kPermuteThreads) void permute_vec_kernel(const char
   set_wave_priority(prio);
   const HookStart t0 = hooks_begin(tr);
   Pacer pc = pace_start(pace);
-  bool first = true;
+  constexpr uint32_t ROUND = UNROLL * kPermuteThreads;  // units of a full round: one pacing period
   const int nwork = nchunks * parts;
   for (int w = blockIdx.x; w < nwork; w += gridDim.x) {
     const int chunk = w / parts;
@@ -240,9 +253,12 @@ __global__ __launch_bounds__(kPermuteThreads) void permute_vec_kernel(const char
       if (head > chunk_bytes) head = chunk_bytes;
       cvec = (chunk_bytes - head) / 16;
       const size_t edge = chunk_bytes - cvec * 16;  // bytes outside the units
-      if (part == parts - 1 && threadIdx.x < edge) {
-        const size_t b = threadIdx.x < head ? threadIdx.x : cvec * 16 + threadIdx.x;
-        d[b] = s[b];
+      if (part == parts - 1 && edge > 0) {
+        pace_trip(pc, 2, ROUND);
+        if (threadIdx.x < edge) {
+          const size_t b = threadIdx.x < head ? threadIdx.x : cvec * 16 + threadIdx.x;
+          d[b] = s[b];
+        }
       }
       s += head;
       d += head;
@@ -251,17 +267,19 @@ __global__ __launch_bounds__(kPermuteThreads) void permute_vec_kernel(const char
     const I hi = (I)(cvec * (part + 1) / parts);
     auto ld = [&](I k) { return __builtin_nontemporal_load(reinterpret_cast<const Unit *>(s + k * (I)16)); };
     auto st = [&](u32x4 v, I k) { __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(d + k * (I)16)); };
-    I i = lo + threadIdx.x;
     u32x4 v[UNROLL];
-    for (; i + (UNROLL - 1) * kPermuteThreads < hi; i += UNROLL * kPermuteThreads) {
-      if (!first) pace_wait(pc);
-      first = false;
+    I base = lo;
+    for (; base + ROUND <= hi; base += ROUND) {
+      pace_trip(pc);
+      const I i = base + threadIdx.x;
 #pragma unroll
       for (int u = 0; u < UNROLL; ++u) v[u] = ld(i + u * kPermuteThreads);
 #pragma unroll
       for (int u = 0; u < UNROLL; ++u) st(v[u], i + u * kPermuteThreads);
     }
-    if (i < hi) {
+    if (base < hi) {
+      pace_trip(pc, (uint32_t)(hi - base), ROUND);
+      const I i = base + threadIdx.x;
 #pragma unroll
       for (int u = 0; u < UNROLL; ++u)
         if (i + u * kPermuteThreads < hi) v[u] = ld(i + u * kPermuteThreads);
@@ -270,6 +288,7 @@ __global__ __launch_bounds__(kPermuteThreads) void permute_vec_kernel(const char
         if (i + u * kPermuteThreads < hi) st(v[u], i + u * kPermuteThreads);
     }
   }
+  pace_end(pc);
   hooks_end(tr, t0);
 }
 
@@ -310,11 +329,11 @@ constexpr int reduce_unroll(int terms, bool off32) {
 // 4 x 224 MiB); the two-wave workgroups take 8, the same bytes per CU.
 constexpr int kPermuteUnroll = 8;
 
-// Period (10 ns ticks) between a wave's trips so that the whole grid moves
-// trip_bytes per period, i.e. streams at rate_gbs; 0 = unpaced.
+// Period (10 ns ticks, rounded up) a wave's trip takes at least, so that the whole
+// grid moves trip_bytes per period, i.e. streams at rate_gbs; 0 = unpaced.
 uint32_t pace_ticks(double trip_bytes, double rate_gbs) {
   if (!(rate_gbs > 0.0)) return 0;
-  double t = trip_bytes / (rate_gbs * 1e9) * 1e8;
+  double t = std::ceil(trip_bytes / (rate_gbs * 1e9) * 1e8);
   if (t < 1.0) t = 1.0;
   if (t > 4.0e9) t = 4.0e9;
   return (uint32_t)t;

@@ -201,3 +201,46 @@ def test_skinny_kn_unit_widths(M, N, K):
     occ.occ_gemm(A, B, C[1], lds_bytes=16 << 10)
     torch.cuda.synchronize()
     assert torch.equal(C[0].view(torch.int16), C[1].view(torch.int16))
+
+
+# a rate is an upper bound at the default grid too, where a workgroup moves as
+# little as one partial round or one position: the transfer takes at least
+# bytes / rate (less 2 % for the two clocks), and not several times that (a
+# workgroup's share is whole positions or rounds of 16 KiB; 30 us for the
+# launches and the waits' granularity).  Results are those of the unpaced call.
+PACED = [("permute", 16, 400 << 10), ("permute", 64, 100 << 10), ("permute", 8, 1 << 20), ("permute", 32, 500 << 10),
+         ("permute", 16, (400 << 10) + 2), ("permute", 7, 16384 * 3 + 16), ("permute", 512, 1001)]
+PACED += [("reduce", n, length) for n in (2, 3, 4, 5, 8, 16, 20) for length in (1 << 16, (1 << 18) + 3, 1 << 20)]
+PACED += [("own", n, length) for n in (1, 2, 7) for length in (1 << 16, (1 << 18) + 64)]
+
+
+@pytest.mark.parametrize("kind,n,size", PACED)
+def test_paced_collective_keeps_the_rate_at_the_default_grid(kind, n, size):
+    g = torch.Generator(device=DEV).manual_seed(size + n)
+    A, B = (torch.ones((64, 64), device=DEV, dtype=torch.bfloat16) for _ in range(2))
+    C = torch.empty((64, 64), device=DEV, dtype=torch.bfloat16)
+    rate = 50.0 if kind == "permute" else 100.0
+    if kind == "permute":
+        src = torch.randint(0, 256, (n * size,), generator=g, device=DEV, dtype=torch.uint8)
+        perm = torch.arange(n - 1, -1, -1, dtype=torch.int32)
+        comm = dict(src=src, dst=torch.zeros_like(src), perm=perm, chunk_bytes=size)
+        want, got, nbytes = src.view(n, size).flip(0).reshape(-1), comm["dst"], 2 * n * size
+    else:
+        x = torch.rand((n, size), generator=g, device=DEV)
+        want, got = torch.empty(size, device=DEV), torch.zeros(size, device=DEV)
+        comm = dict(bufs=x, out=got)
+        nbytes = 4 * (n + 1) * size
+        if kind == "own":
+            A, B = torch.ones((8, 8), device=DEV, dtype=torch.bfloat16), torch.ones((8, size // 8), device=DEV, dtype=torch.bfloat16)
+            C = torch.empty((3, 8, size // 8), device=DEV, dtype=torch.bfloat16)
+            comm["reduce_own"] = True
+            nbytes += 2 * size
+            occ.share_reduce_own(torch.full((size,), 8.0, device=DEV, dtype=torch.bfloat16), x, want)
+        else:
+            occ.share_reduce(x, want)
+    r = occ.run_overlap(A, B, C, n_iter=3, reps=3, warmup=1, comm_priority=0, comm_rate_gbs=rate,
+                        flags=occ.OCC_RUN_ISO | occ.OCC_RUN_PACE_ALL, **comm)
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.uint8), want.view(torch.uint8))
+    paced_us = nbytes / rate * 1e-3
+    assert 0.98 * paced_us <= r["t_comm_ms"] * 1e3 <= 2.0 * paced_us + 30.0, (r["t_comm_ms"] * 1e3, paced_us)
