@@ -52,7 +52,10 @@ typedef enum occ_status {
  *   C : M x N, row-major bf16, ldc = N.  Rounded to nearest-even from fp32.
  * lds_bytes is the EXTRA dynamic LDS each GEMM workgroup reserves on top of
  * the LDS its tile uses (S_tile).  It is never touched; it only lowers the
- * number of GEMM workgroups that fit on a CU (Section 3.1, S_blk).
+ * number of GEMM workgroups that fit on a CU (Section 3.1, S_blk).  The tile
+ * is the one of lds_bytes == 0 wherever it fits beside the pad; a pad that
+ * only a smaller tile leaves room for takes that tile (occ_gemm_plan_query
+ * tells) or, on large shapes, is refused.
  * Requirements: M, N, K >= 0; K % 8 == 0 and N % 8 == 0 (16-byte rows);
  * A, B, C 16-byte aligned; C must not overlap A or B; K at most 4 M and N at
  * most 16 M (an operand tile is addressed with 32-bit offsets; larger is
@@ -76,7 +79,7 @@ enum {
   OCC_GEMM_AUTO = 0,
   /* B stored K x N (occ_gemm) */
   OCC_GEMM_KN_256x256x64_8W_2ST = 32,   /* direct-to-LDS; default for large shapes */
-  OCC_GEMM_KN_SKINNY_4W_2ST = 33,       /* M <= 16: 128-column units over the whole K; default for M <= 16 */
+  OCC_GEMM_KN_SKINNY_4W_2ST = 33,       /* M <= 16: units of 32, 64 or 128 columns (by N) over the whole K; default for M <= 16 */
   OCC_GEMM_KN_128x128x64_4W_3ST = 35,   /* register-pipelined (8 waves); default for mid-size shapes */
   OCC_GEMM_KN_OPT1_64x64x32 = 36,       /* Table 1 opt1, one stage */
   OCC_GEMM_KN_OPT2_64x64x64 = 37,       /* Table 1 opt2, one stage */
@@ -175,7 +178,8 @@ int occ_gemm_bt_plan_query(int M, int N, int K, size_t lds_bytes, int variant, i
  * the device's per-workgroup LDS limit and its LDS per CU, in bytes; so a
  * caller can size lds_bytes (S_tile + pad <= max_lds_per_wg; resident
  * workgroups per CU <= lds_per_cu / (S_tile + pad)).  occ_gemm_plan_query
- * gives the same for any shape and variant.  OCC_EINVAL for a null pointer;
+ * gives the same for any shape and variant; S_tile of its plan without a pad
+ * is that of every pad with S_tile + pad <= max_lds_per_wg.  OCC_EINVAL for a null pointer;
  * OCC_ENODEV without a gfx950 device.
  */
 int occ_gemm_info(int *tile_lds_bytes, int *max_lds_per_wg, int *lds_per_cu);

@@ -212,10 +212,9 @@ const Variant *find_variant(int id) {
 int ceil_div(long long a, long long b) { return (int)((a + b - 1) / b); }
 
 // The form of variant `id` for a call: variant 33 takes the widest units that
-// leave no CU without one, down to a quarter of the CUs with 32 columns.  With
-// a pad it keeps the 128-column units, whose LDS the pad is meant to add to.
+// leave no CU without one, down to a quarter of the CUs with 32 columns.
 const Variant *variant_form(const GemmCall &c, int id, int num_cus) {
-  if (id == 33 && c.lds_bytes == 0) {
+  if (id == 33) {
     if (ceil_div(c.N, 32) <= num_cus / 4) return &kSkinnyKn32;
     if (ceil_div(c.N, 64) <= num_cus) return &kSkinnyKn64;
   }
@@ -253,25 +252,53 @@ const TileCost kTileCosts[] = {
     {9, 39, 1.6, 0.4, 0.45, true},    // 64x64
 };
 
-// The kernel for a shape.  M <= 16: skinny.  A pad asks for a given residency
-// of the GEMM's workgroups, so with one the tile follows from the tile count
-// alone: the largest of 256x256, 128x128 and 64x64 that still gives one
-// 256x256 tile per CU or one 128x128 tile per two CUs.  Without one it is the
-// tile with the least estimated time, except that a B which is read once and
+// The tile for M > 16 among those whose LDS fits in `room` bytes, 0 if none: the
+// one with the least estimated time, except that a B which is read once and
 // comes from memory goes to a tile that covers M and whose loads can be
 // non-temporal: the tile then matters little, the loads much.  That is 128x128,
 // or for N x K B and M <= 64 64x128 with k-steps of 128, which read 256-byte
 // pieces of B's rows (64x28672x8192 98 -> 92 us, 64x65536x4096 114 -> 104; K x N
-// B has 256-byte pieces in both and no difference).  A K or N
-// beyond what the chosen tile addresses with 32-bit offsets takes the 64x64
-// tile, and a K beyond that (B N x K) the register-staged opt2 tile.
+// B has 256-byte pieces in both and no difference).
 //
 // The 32-row tiles are left to K > kMaxKLaunch.  Up to there a launch is as long
 // as the host needs to enqueue the next (512x512x512: 4.7 us, 3.9 with them, of a
 // call's 6), and a quarter of the workgroups leave the other CUs to a collective;
 // beyond it they pay (20x5552x568 5.3 -> 4.3, 27x1512x1200 6.7 -> 5.4).
 constexpr int kMaxKLaunch = 512;
-int auto_variant(const GemmCall &c, int num_cus) {
+int fastest_tile(const GemmCall &c, int num_cus, int room) {
+  const int M = c.M, N = c.N, K = c.K;
+  const int mid = c.b_kn ? 35 : 14;
+  if (M <= 128 && b_exceeds_llc(N, K)) {
+    if (!c.b_kn && M <= 64 && find_variant(13)->lds <= room) return 13;
+    if (find_variant(mid)->lds <= room) return mid;
+  }
+  const int slots = c.grid_cap > 0 && c.grid_cap < num_cus ? c.grid_cap : num_cus;
+  double best = 0;
+  int v = 0;
+  for (const TileCost &tc : kTileCosts) {
+    const Variant *pv = find_variant(c.b_kn ? tc.id_kn : tc.id_nk);
+    if (pv->lds > room || (pv->bm == 32 && K <= kMaxKLaunch)) continue;
+    const double tiles = (double)ceil_div(M, pv->bm) * ceil_div(N, pv->bn);
+    const double rounds = tc.shared ? std::max(1.0, tiles / slots) : std::ceil(tiles / slots);
+    const double t = tc.launch + rounds * (tc.fixed + tc.step * ceil_div(K, 64));
+    if (best == 0 || t < best) {
+      best = t;
+      v = pv->id;
+    }
+  }
+  return v;
+}
+
+// The kernel for a shape.  M <= 16: skinny.  Otherwise the fastest tile, with or
+// without a pad, so that a pad changes its residency and nothing else.  Where the
+// tile does not fit beside the pad, the fastest one that does takes its place, but
+// only up to the pads that the largest of 256x256, 128x128 and 64x64 that gives a
+// 256x256 tile per CU or a 128x128 one per two CUs leaves room for: larger pads
+// are refused (a pad asks for a residency; it is never clamped, nor met by an ever
+// smaller tile).  A K or N beyond what the chosen tile addresses with 32-bit
+// offsets takes the 64x64 tile, and a K beyond that (B N x K) the register-staged
+// opt2 tile.
+int auto_variant(const GemmCall &c, const DeviceInfo &di) {
   const int M = c.M, N = c.N, K = c.K;
   const bool b_kn = c.b_kn;
   if (M <= 16) {
@@ -282,33 +309,26 @@ int auto_variant(const GemmCall &c, int num_cus) {
     return 21;
   }
   const int large = b_kn ? 32 : 16, mid = b_kn ? 35 : 14, small = b_kn ? 39 : 9;
-  int v = small;
-  if (c.lds_bytes > 0) {
-    long long big = (long long)ceil_div(M, 256) * ceil_div(N, 256);
-    long long mids = (long long)ceil_div(M, 128) * ceil_div(N, 128);
-    v = big >= num_cus ? large : (mids >= num_cus / 2 ? mid : small);
-  } else if (M <= 128 && b_exceeds_llc(N, K)) {
-    v = !b_kn && M <= 64 ? 13 : mid;
-  } else {
-    const int slots = c.grid_cap > 0 && c.grid_cap < num_cus ? c.grid_cap : num_cus;
-    double best = 0;
-    for (const TileCost &tc : kTileCosts) {
-      const Variant *pv = find_variant(b_kn ? tc.id_kn : tc.id_nk);
-      if (pv->bm == 32 && K <= kMaxKLaunch) continue;
-      const double tiles = (double)ceil_div(M, pv->bm) * ceil_div(N, pv->bn);
-      const double rounds = tc.shared ? std::max(1.0, tiles / slots) : std::ceil(tiles / slots);
-      const double t = tc.launch + rounds * (tc.fixed + tc.step * ceil_div(K, 64));
-      if (best == 0 || t < best) {
-        best = t;
-        v = pv->id;
-      }
+  auto addressable = [&](int v) {
+    const Variant *pv = find_variant(v);
+    if ((pv->kmax > 0 && K > pv->kmax) || (pv->nmax > 0 && N > pv->nmax)) {
+      v = small;
+      pv = find_variant(v);
+      if (pv->kmax > 0 && K > pv->kmax && !b_kn) v = 7;
     }
-  }
-  const Variant *pv = find_variant(v);
-  if ((pv->kmax > 0 && K > pv->kmax) || (pv->nmax > 0 && N > pv->nmax)) {
-    v = small;
-    pv = find_variant(v);
-    if (pv->kmax > 0 && K > pv->kmax && !b_kn) v = 7;
+    return v;
+  };
+  int v = addressable(fastest_tile(c, di.num_cus, di.max_lds_per_wg));
+  if (c.lds_bytes > 0 && c.lds_bytes <= (size_t)di.max_lds_per_wg) {
+    const int room = di.max_lds_per_wg - (int)c.lds_bytes;
+    auto fits = [&](int id) { return find_variant(id)->lds <= room; };
+    const long long big = (long long)ceil_div(M, 256) * ceil_div(N, 256);
+    const long long mids = (long long)ceil_div(M, 128) * ceil_div(N, 128);
+    const int by_count = addressable(big >= di.num_cus ? large : (mids >= di.num_cus / 2 ? mid : small));
+    if (!fits(v) && fits(by_count)) {
+      v = fastest_tile(c, di.num_cus, room);
+      v = v != 0 && fits(addressable(v)) ? addressable(v) : by_count;
+    }
   }
   return v;
 }
@@ -359,7 +379,7 @@ int gemm_launch_plan(const GemmCall &c, occ_gemm_plan *plan) {
   int st = current_device_info(&di);
   if (st != OCC_OK) return st;
   int variant = c.variant;
-  if (variant == 0) variant = auto_variant(c, di->num_cus);
+  if (variant == 0) variant = auto_variant(c, *di);
   return fill_plan(c, variant, *di, plan);
 }
 
@@ -408,15 +428,16 @@ int gemm_launch(const GemmCall &c, hipStream_t s) {
     hipLaunchKernelGGL(fn, dim3(p.grid), dim3(v->threads), dyn, s, A, B, C, c.M, c.N, c.K,
                        tiles_m, tiles_n, c.priority, c.trace);
   } else {
-    // the attribute matters to pads only, and with a pad a variant has one width
+    // the attribute matters to pads only
     const bool through = c.trace.release && v->skinny_through != nullptr;
     const SkinnyFn fn = through ? v->skinny_through : v->skinny;
-    static bool attr_set_skinny[kMaxDevices][kMaxVariantId + 1][2] = {};
-    if (c.lds_bytes > 0 && !attr_set_skinny[dev][v->id][through]) {
+    const int width = v->bn >= 128 ? 0 : v->bn >= 64 ? 1 : 2;  // variant 33's forms
+    static bool attr_set_skinny[kMaxDevices][kMaxVariantId + 1][2][3] = {};
+    if (c.lds_bytes > 0 && !attr_set_skinny[dev][v->id][through][width]) {
       if (hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
                               p.max_lds_per_wg - v->lds) != hipSuccess)
         return OCC_EHIP;
-      attr_set_skinny[dev][v->id][through] = true;
+      attr_set_skinny[dev][v->id][through][width] = true;
     }
     hipLaunchKernelGGL(fn, dim3(p.grid), dim3(v->threads), (int)c.lds_bytes, s, A, B, C, c.M, c.N, c.K,
                        c.priority, c.trace);

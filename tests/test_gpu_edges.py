@@ -159,7 +159,7 @@ def test_shape_rule_takes_every_tile_and_gives_the_same_bits():
         torch.cuda.synchronize()
         assert torch.equal(C[0].view(torch.int16), C[2].view(torch.int16)), (M, N, K)
         assert torch.equal(C[1].view(torch.int16), C[2].view(torch.int16)), (M, N, K)
-    # a pad keeps the choice by tile count, and every pad that fitted it
+    # a pad beside which the tile does not fit, but the one by tile count does
     assert occ.occ_gemm_plan_query(512, 1024, 1536, 128 << 10)["kernel_id"] == 39
 
 
@@ -180,8 +180,8 @@ def test_streamed_weight_takes_non_temporal_loads(layout, M, kernel):
     assert torch.equal(C[0].view(torch.int16), C[1].view(torch.int16))
 
 
-# skinny K x N: 32-, 64- and 128-column units at and around their limits, the
-# widest with a pad for every N, K of less than a block per wave and ragged
+# skinny K x N: 32-, 64- and 128-column units at and around their limits, the same
+# ones with a pad, K of less than a block per wave and ragged
 @pytest.mark.parametrize("M,N,K", [(1, 8, 8), (5, 40, 72), (16, 2048, 200), (13, 2056, 136), (16, 2120, 1032),
                                    (7, 16384, 40), (16, 16392, 64)])
 def test_skinny_kn_unit_widths(M, N, K):
@@ -189,18 +189,65 @@ def test_skinny_kn_unit_widths(M, N, K):
     plan = occ.occ_gemm_plan_query(M, N, K)
     want = 32 if -(-N // 32) <= cus // 4 else 64 if -(-N // 64) <= cus else 128
     assert plan["kernel_id"] == 33 and plan["tile_n"] == want and plan["tiles"] == -(-N // want)
-    assert occ.occ_gemm_plan_query(M, N, K, 16 << 10)["tile_n"] == 128
+    # a pad changes the residency, not the kernel: up to the last byte that fits
+    for pad in (1, 16 << 10, plan["max_lds_per_wg"] - plan["tile_lds_bytes"]):
+        p = occ.occ_gemm_plan_query(M, N, K, pad)
+        assert p["feasible"] and p["tile_n"] == want and p["tile_lds_bytes"] == plan["tile_lds_bytes"], pad
+    assert not occ.occ_gemm_plan_query(M, N, K, pad + 1)["feasible"]
     for cap in (0, 3):
         got, ref = int_gemm(M, N, K, "kn", 33, cap, seed=N + K)
         assert np.array_equal(got, ref), cap
     g = torch.Generator(device=DEV).manual_seed(N)
     A = torch.randn((M, K), generator=g, device=DEV).to(torch.bfloat16)
     B = torch.randn((K, N), generator=g, device=DEV).to(torch.bfloat16)
-    C = [torch.full((M, N), float("nan"), device=DEV, dtype=torch.bfloat16) for _ in range(2)]
+    C = [torch.full((M, N), float("nan"), device=DEV, dtype=torch.bfloat16) for _ in range(3)]
     occ.occ_gemm(A, B, C[0])
     occ.occ_gemm(A, B, C[1], lds_bytes=16 << 10)
+    occ.occ_gemm(A, B, C[2], lds_bytes=pad)
     torch.cuda.synchronize()
     assert torch.equal(C[0].view(torch.int16), C[1].view(torch.int16))
+    assert torch.equal(C[0].view(torch.int16), C[2].view(torch.int16))
+
+
+def tile_by_count(M, N, cus):
+    """LDS of the largest of 256x256, 128x128 and 64x64 that still gives a 256x256 tile
+    per CU or a 128x128 one per two CUs: the pads it leaves room for are never refused."""
+    if -(-M // 256) * -(-N // 256) >= cus:
+        return 128 << 10
+    return (96 << 10) if -(-M // 128) * -(-N // 128) >= cus // 2 else (32 << 10)
+
+
+# one shape per tile of the automatic choice, and streamed weights
+@pytest.mark.parametrize("layout", ["kn", "nk"])
+@pytest.mark.parametrize("M,N,K", [(4096, 4096, 512), (1792, 2816, 1024), (2048, 2048, 512), (1024, 2048, 1024),
+                                   (1024, 1024, 1536), (640, 512, 256), (512, 1024, 1536), (512, 512, 1536),
+                                   (40, 16520, 8192), (70, 16520, 8192), (4104, 4104, 1024)])
+def test_pad_keeps_the_tile_wherever_it_fits(layout, M, N, K):
+    q = occ.occ_gemm_plan_query if layout == "kn" else occ.occ_gemm_bt_plan_query
+    p0 = q(M, N, K)
+    limit, tile = p0["max_lds_per_wg"], p0["tile_lds_bytes"]
+    for pad in (1, 16, 1 << 10, 8 << 10, 16 << 10, 32 << 10, (32 << 10) + 16, 64 << 10, 96 << 10, 128 << 10,
+                (128 << 10) + 16, limit - tile, limit - tile + 1, limit + 16):
+        p = q(M, N, K, pad)
+        if tile + pad <= limit:
+            assert p["feasible"] and p["kernel_id"] == p0["kernel_id"], pad
+            assert p["wg_per_cu"] <= p0["wg_per_cu"], pad
+        else:
+            assert p["feasible"] == (tile_by_count(M, N, p0["num_cus"]) + pad <= limit), pad
+    # the pad that takes one resident workgroup away is one to offer wherever there are two
+    if p0["wg_per_cu"] > 1:
+        p = q(M, N, K, p0["lds_per_cu"] // p0["wg_per_cu"] + 1 - tile)
+        assert p["kernel_id"] == p0["kernel_id"] and p["wg_per_cu"] == p0["wg_per_cu"] - 1
+    g = torch.Generator(device=DEV).manual_seed(M)
+    A = torch.randn((M, K), generator=g, device=DEV).to(torch.bfloat16)
+    B = torch.randn((K, N) if layout == "kn" else (N, K), generator=g, device=DEV).to(torch.bfloat16)
+    C = [torch.full((M, N), float("nan"), device=DEV, dtype=torch.bfloat16) for _ in range(2)]
+    f = occ.occ_gemm if layout == "kn" else occ.occ_gemm_bt
+    f(A, B, C[0])
+    for pad in (16, limit - tile, min(limit - tile_by_count(M, N, p0["num_cus"]), 128 << 10)):
+        f(A, B, C[1].fill_(float("nan")), lds_bytes=pad)
+        torch.cuda.synchronize()
+        assert torch.equal(C[0].view(torch.int16), C[1].view(torch.int16)), pad
 
 
 # a rate is an upper bound at the default grid too, where a workgroup moves as
