@@ -235,7 +235,12 @@ bool b_exceeds_llc(int N, int K) { return (long long)N * K * 2 > (256ll << 20); 
 // chosen by tile count alone.  The 32-row tiles win where 64x64 ones leave half
 // of the CUs or more idle: on 39 more shapes of 17..1200 (M), 128..28672 (N) and
 // 520..8192 (K) the choice with them is within 0.5 (N x K) and 0.1 % (K x N) of the
-// fastest on average (19 and 2 % at most).
+// fastest on average (19 and 3 % at most).  On 35 shapes of K 64..512 it is within
+// 3 and 1.5 % (16 and 9 % at most: up to K = 256 the 64x64 tile's estimate is too
+// low against 32x32, 134x352x256 N x K 3.8 us and 3.3), and up to 26 % faster than
+// with the 64x64 tile wherever it takes a 32-row one (512x512x512 4.6 -> 3.8 N x K,
+// 4.6 -> 4.0 K x N; the schedule of that GEMM and a 4 x 2^18 chunk sum with the
+// device counter 114 -> 102 us for 10 iterations, sequential 71 -> 66).
 struct TileCost {
   int id_nk, id_kn;
   double launch, fixed, step;
@@ -259,12 +264,6 @@ const TileCost kTileCosts[] = {
 // or for N x K B and M <= 64 64x128 with k-steps of 128, which read 256-byte
 // pieces of B's rows (64x28672x8192 98 -> 92 us, 64x65536x4096 114 -> 104; K x N
 // B has 256-byte pieces in both and no difference).
-//
-// The 32-row tiles are left to K > kMaxKLaunch.  Up to there a launch is as long
-// as the host needs to enqueue the next (512x512x512: 4.7 us, 3.9 with them, of a
-// call's 6), and a quarter of the workgroups leave the other CUs to a collective;
-// beyond it they pay (20x5552x568 5.3 -> 4.3, 27x1512x1200 6.7 -> 5.4).
-constexpr int kMaxKLaunch = 512;
 int fastest_tile(const GemmCall &c, int num_cus, int room) {
   const int M = c.M, N = c.N, K = c.K;
   const int mid = c.b_kn ? 35 : 14;
@@ -277,7 +276,7 @@ int fastest_tile(const GemmCall &c, int num_cus, int room) {
   int v = 0;
   for (const TileCost &tc : kTileCosts) {
     const Variant *pv = find_variant(c.b_kn ? tc.id_kn : tc.id_nk);
-    if (pv->lds > room || (pv->bm == 32 && K <= kMaxKLaunch)) continue;
+    if (pv->lds > room) continue;
     const double tiles = (double)ceil_div(M, pv->bm) * ceil_div(N, pv->bn);
     const double rounds = tc.shared ? std::max(1.0, tiles / slots) : std::ceil(tiles / slots);
     const double t = tc.launch + rounds * (tc.fixed + tc.step * ceil_div(K, 64));

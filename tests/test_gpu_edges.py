@@ -145,7 +145,10 @@ def test_shape_rule_takes_every_tile_and_gives_the_same_bits():
     # one shape per tile of the automatic choice; all tiles sum over k in one order
     for (M, N, K), kn, nk in (((4096, 4096, 512), 32, 16), ((1792, 2816, 1024), 40, 10), ((2048, 2048, 512), 35, 14),
                               ((1024, 2048, 1024), 41, 11), ((1024, 1024, 1536), 42, 12), ((640, 512, 256), 39, 9),
-                              ((512, 1024, 1536), 43, 17), ((512, 512, 1536), 44, 18)):
+                              ((512, 1024, 1536), 43, 17), ((512, 512, 1536), 44, 18),
+                              # the 32-row tiles have no limit in K of their own
+                              ((1024, 512, 512), 43, 17), ((512, 512, 512), 44, 18), ((64, 1024, 512), 44, 18),
+                              ((64, 1024, 520), 44, 18), ((300, 696, 400), 44, 18)):
         assert occ.occ_gemm_plan_query(M, N, K)["kernel_id"] == kn, (M, N, K)
         assert occ.occ_gemm_bt_plan_query(M, N, K)["kernel_id"] == nk, (M, N, K)
         g = torch.Generator(device=DEV).manual_seed(M)

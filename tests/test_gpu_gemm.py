@@ -193,15 +193,19 @@ def test_gemm_info_matches_plan():
 
 def test_auto_choice_by_shape():
     # large: 256x256; mid: 128x128 three stages; small: the opt2 tile with
-    # two stages; M <= 16: the skinny kernel
+    # two stages where it has enough of them or little K, else 32-row tiles
+    # (512^3: 64 64x64 tiles 4.5 us a launch, 256 32x32 ones 3.9; the same
+    # bits); M <= 16: the skinny kernel
     assert occ.occ_gemm_plan_query(8192, 8192, 8192)["kernel_id"] == 32
     assert occ.occ_gemm_plan_query(2048, 2048, 4096)["kernel_id"] == 35
-    assert occ.occ_gemm_plan_query(512, 512, 512)["kernel_id"] == 39
+    assert occ.occ_gemm_plan_query(512, 512, 512)["kernel_id"] == 44
+    assert occ.occ_gemm_plan_query(1024, 1024, 512)["kernel_id"] == 39
     assert occ.occ_gemm_plan_query(16, 28672, 8192)["kernel_id"] == 33
     assert occ.occ_gemm_plan_query(17, 28672, 8192)["kernel_id"] == 35    # 224 128x128 tiles
     assert occ.occ_gemm_bt_plan_query(8192, 8192, 8192)["kernel_id"] == 16
     assert occ.occ_gemm_bt_plan_query(2048, 2048, 4096)["kernel_id"] == 14
-    assert occ.occ_gemm_bt_plan_query(512, 512, 512)["kernel_id"] == 9
+    assert occ.occ_gemm_bt_plan_query(512, 512, 512)["kernel_id"] == 18
+    assert occ.occ_gemm_bt_plan_query(1024, 1024, 512)["kernel_id"] == 9
 
 
 def test_paper_tiles_lds_footprint():
