@@ -295,8 +295,8 @@ int fastest_tile(const GemmCall &c, int num_cus, int room) {
 // 256x256 tile per CU or a 128x128 one per two CUs leaves room for: larger pads
 // are refused (a pad asks for a residency; it is never clamped, nor met by an ever
 // smaller tile).  A K or N beyond what the chosen tile addresses with 32-bit
-// offsets takes the 64x64 tile, and a K beyond that (B N x K) the register-staged
-// opt2 tile.
+// offsets takes the 64x64 tile.  A K beyond that one's takes the register-staged
+// opt2 tile (B N x K) or is refused (K x N), also where a 32x32 tile would reach it.
 int auto_variant(const GemmCall &c, const DeviceInfo &di) {
   const int M = c.M, N = c.N, K = c.K;
   const bool b_kn = c.b_kn;
@@ -309,13 +309,9 @@ int auto_variant(const GemmCall &c, const DeviceInfo &di) {
   }
   const int large = b_kn ? 32 : 16, mid = b_kn ? 35 : 14, small = b_kn ? 39 : 9;
   auto addressable = [&](int v) {
+    if (K > find_variant(small)->kmax) return b_kn ? small : 7;
     const Variant *pv = find_variant(v);
-    if ((pv->kmax > 0 && K > pv->kmax) || (pv->nmax > 0 && N > pv->nmax)) {
-      v = small;
-      pv = find_variant(v);
-      if (pv->kmax > 0 && K > pv->kmax && !b_kn) v = 7;
-    }
-    return v;
+    return (pv->kmax > 0 && K > pv->kmax) || (pv->nmax > 0 && N > pv->nmax) ? small : v;
   };
   int v = addressable(fastest_tile(c, di.num_cus, di.max_lds_per_wg));
   if (c.lds_bytes > 0 && c.lds_bytes <= (size_t)di.max_lds_per_wg) {

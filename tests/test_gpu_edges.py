@@ -294,3 +294,15 @@ def test_paced_collective_keeps_the_rate_at_the_default_grid(kind, n, size):
     assert torch.equal(got.view(torch.uint8), want.view(torch.uint8))
     paced_us = nbytes / rate * 1e-3
     assert 0.98 * paced_us <= r["t_comm_ms"] * 1e3 <= 2.0 * paced_us + 30.0, (r["t_comm_ms"] * 1e3, paced_us)
+
+
+def test_k_beyond_the_64x64_tile_is_refused_or_register_staged():
+    # also for the shapes whose 32x32 tile could address twice that K
+    for M, N in ((17, 64), (32, 8), (300, 200), (4096, 4096)):
+        k = 1 << 24
+        assert occ.occ_gemm_plan_query(M, N, k)["feasible"] and occ.occ_gemm_bt_plan_query(M, N, k)["kernel_id"] != 7
+        for K in (k + 8, (1 << 25) + 8):
+            with pytest.raises(occ.OccError) as e:
+                occ.occ_gemm_plan_query(M, N, K)
+            assert e.value.status == occ.OCC_EINVAL, (M, N, K)
+            assert occ.occ_gemm_bt_plan_query(M, N, K)["kernel_id"] == 7, (M, N, K)
