@@ -193,8 +193,8 @@ int occ_gemm_info(int *tile_lds_bytes, int *max_lds_per_wg, int *lds_per_cu);
  * definition (no reassociation, no contraction, denormals kept).
  *   bufs    : HOST array of nchunks device pointers, 1 <= nchunks <= 64.
  *   out     : device fp32 buffer of len elements; must not overlap any bufs[c].
- * len == 0 is a no-op.  Any alignment is accepted; 4-byte-aligned buffers
- * take the vectorised path.
+ * Buffers are aligned to their 4-byte elements (OCC_EINVAL otherwise) and are
+ * read 16 bytes at a time at any such alignment.  len == 0 is a no-op.
  */
 int share_reduce(const float *const *bufs, int nchunks, size_t len, float *out, void *stream);
 
@@ -228,14 +228,14 @@ int share_permute(const void *src, void *dst, const int32_t *perm, int nchunks, 
  *   out[j] = (((f32(own[j]) + peers[0][j]) + peers[1][j]) + ...) + peers[n-1][j]
  * in IEEE binary32, strict left-to-right, f32() the exact widening of a bf16
  * bit pattern.  Bit-identical to that definition.
- *   own   : device bf16 buffer of len elements (2-byte aligned).
+ *   own   : device bf16 buffer of len elements (2-byte aligned; peers and out
+ *           4-byte aligned; OCC_EINVAL otherwise).
  *   peers : HOST array of npeers device fp32 pointers, 0 <= npeers <= 63
  *           (may be NULL when npeers == 0).
  *   out   : device fp32 buffer of len elements; must not overlap own or any
  *           peer.
  *   wgs, priority : as share_reduce_ex.
- * len == 0 is a no-op.  Buffers aligned to their elements take the vectorised
- * path.
+ * len == 0 is a no-op.
  */
 int share_reduce_own(const void *own, const float *const *peers, int npeers, size_t len, float *out,
                      int wgs, int priority, void *stream);

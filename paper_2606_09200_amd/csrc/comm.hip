@@ -55,7 +55,7 @@ struct ChunkPtrs {
   const float *p[kMaxReduceChunks];
 };
 
-// Vector path.  Element j's sum is acc = c0[j]; acc = acc + c1[j]; ... exactly
+// Chunk sum.  Element j's sum is acc = c0[j]; acc = acc + c1[j]; ... exactly
 // in chunk order; the loads of all chunks for UNROLL positions are issued
 // before any addition.  A position is 4 elements, loaded with one 16-byte load
 // per chunk at the element's own 4-byte alignment: chunks are often rows of
@@ -66,7 +66,7 @@ struct ChunkPtrs {
 // first lanes.
 //
 // What bounds it is bytes in flight: the default grid is one workgroup of two
-// waves per CU, so a lane needs 12-16 loads outstanding.  NC >= 0 (the number
+// waves per CU, so a lane needs 8-16 loads outstanding.  NC >= 0 (the number
 // of fp32 chunks) therefore has its own instantiation for every term count up
 // to 16, with UNROLL from reduce_unroll; NC < 0 folds `nchunks` chunks in
 // batches of 8 loads.  Measured on MI355X at 0.5 GB of chunks, 256 workgroups:
@@ -197,23 +197,6 @@ __global__ __launch_bounds__(kReduceThreads) void reduce_vec_kernel(ChunkPtrs cp
   hooks_end(tr, t0);
 }
 
-// Scalar path, one element at a time: for fp32 buffers that are not even
-// 4-byte aligned.
-__global__ __launch_bounds__(kReduceThreads) void reduce_scalar_kernel(ChunkPtrs cp, int nchunks, size_t len,
-                                                                       float *__restrict__ out,
-                                                                       const uint16_t *__restrict__ own,
-                                                                       int prio, KHooks tr) {
-  set_wave_priority(prio);
-  const HookStart t0 = hooks_begin(tr);
-  const size_t stride = (size_t)gridDim.x * kReduceThreads;
-  for (size_t j = (size_t)blockIdx.x * kReduceThreads + threadIdx.x; j < len; j += stride) {
-    float acc = own != nullptr ? widen_own(own + j) : cp.p[0][j];
-    for (int c = own != nullptr ? 0 : 1; c < nchunks; ++c) acc = acc + cp.p[c][j];
-    out[j] = acc;
-  }
-  hooks_end(tr, t0);
-}
-
 struct PermTable {
   int32_t p[kMaxPermuteChunks];
 };
@@ -312,8 +295,8 @@ int clamp_wgs(size_t work_units, int wanted, int threads) {
 
 // Positions per lane per trip of the vector chunk sum for a number of terms
 // (fp32 chunks plus the own term); the launch table and the pacing period
-// both take it from here.  12-16 loads in flight per lane as far as 64 VGPRs
-// hold them; 64-bit offsets need registers of their own.
+// both take it from here.  8-16 loads in flight per lane (a single term 4), as far
+// as 64 VGPRs hold them; 64-bit offsets need registers of their own.
 constexpr int kExactTerms = 16;  // term counts with an instantiation of their own
 constexpr bool exact_terms(int terms, bool off32) {
   return off32 ? terms <= kExactTerms : (terms == 2 || terms == 4 || terms == 8 || terms == 16);
@@ -371,28 +354,15 @@ int reduce_launch(const ReduceCall &c, hipStream_t s) {
   ChunkPtrs cp;
   memset(&cp, 0, sizeof cp);
   const bool own = c.own != nullptr;
-  auto aligned = [](const void *p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; };
-  bool vec = aligned(c.out, 4) && aligned(c.own, 2);
-  for (int i = 0; i < c.nchunks; ++i) {
-    cp.p[i] = c.bufs[i];
-    vec = vec && aligned(c.bufs[i], 4);
-  }
   const int wgs = c.wgs > 0 ? c.wgs : reduce_default_wgs(c);
   const int prio = c.priority;
   // a dependency wait is acknowledged by every workgroup of the kernel
   KHooks tr = c.trace;
-  if (!vec) {
-    const int g = clamp_wgs(c.len, wgs, kReduceThreads);
-    if (tr.wait != nullptr) tr.ack_target = (uint32_t)g;
-    hipLaunchKernelGGL(reduce_scalar_kernel, dim3(g), dim3(kReduceThreads), 0, s, cp, c.nchunks, c.len, c.out,
-                       c.own, prio, tr);
-    return hipGetLastError() == hipSuccess ? OCC_OK : OCC_EHIP;
-  }
   // positions start at out's first 16-byte boundary; with an own term at
   // element 0, which keeps its 8-byte loads aligned
   size_t head = own ? 0 : ((16 - (reinterpret_cast<uintptr_t>(c.out) & 15)) & 15) / 4;
   if (head > c.len) head = c.len;
-  for (int i = 0; i < c.nchunks; ++i) cp.p[i] += head;
+  for (int i = 0; i < c.nchunks; ++i) cp.p[i] = c.bufs[i] + head;
   const size_t nvec = (c.len - head) / 4;
   const int tail = (int)(c.len - head - nvec * 4);
   const int g = clamp_wgs(nvec, wgs, kReduceThreads);
@@ -411,7 +381,7 @@ int reduce_launch(const ReduceCall &c, hipStream_t s) {
     else launch_reduce<false, OWN>(c.nchunks, g, s, cp, nvec, out, c.own, (int)head, tail, prio, pace, tr);
   };
   if (!own) launch(std::integral_constant<int, kOwnNone>{});
-  else if (aligned(c.own, 8)) launch(std::integral_constant<int, kOwnDevice>{});
+  else if ((reinterpret_cast<uintptr_t>(c.own) & 7u) == 0) launch(std::integral_constant<int, kOwnDevice>{});
   else launch(std::integral_constant<int, kOwnPlain>{});
   return hipGetLastError() == hipSuccess ? OCC_OK : OCC_EHIP;
 }

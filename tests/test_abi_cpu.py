@@ -142,6 +142,10 @@ def test_reduce_own_argument_errors(L):
     assert L.share_reduce_own(own, None, 2, 16, out, 0, 0, None) == -1
     assert L.share_reduce_own(None, arr, 2, 16, out, 0, 0, None) == -1
     assert L.share_reduce_own(P(0x9000001), arr, 2, 16, out, 0, 0, None) == -1  # own not 2-byte aligned
+    odd = (ctypes.c_void_p * 2)(0x100000, 0x200002)
+    assert L.share_reduce_own(own, odd, 2, 16, out, 0, 0, None) == -1         # fp32 off 4 bytes: a peer,
+    assert L.share_reduce_own(own, arr, 2, 16, P(0xA000002), 0, 0, None) == -1  # the output,
+    assert L.share_reduce(arr, 2, 16, P(0xA000001), None) == -1               # of either form
     assert L.share_reduce_own(own, arr, 2, 16, P(0x9000000 + 8), 0, 0, None) == -4  # out over own
     assert L.share_reduce_own(own, arr, 2, 16, P(0x100000 + 4), 0, 0, None) == -4   # out over a peer
     assert L.share_reduce_own(own, arr, 2, 16, out, 0, 4, None) == -1         # priority
