@@ -306,3 +306,43 @@ def test_k_beyond_the_64x64_tile_is_refused_or_register_staged():
                 occ.occ_gemm_plan_query(M, N, K)
             assert e.value.status == occ.OCC_EINVAL, (M, N, K)
             assert occ.occ_gemm_bt_plan_query(M, N, K)["kernel_id"] == 7, (M, N, K)
+
+
+# Schedules in a row on the same buffers, as a program runs them: each pass has other
+# operands, so a line of C left in some L2 by the pass before (or by the checks
+# between them, which read C) would show in the sum.  One iteration per pass checks
+# every output that is read; three check the last.  Every kernel with device-scope
+# stores, wide and narrow rows, C of a few KiB and of several MiB, 1 to 8 terms.
+@pytest.mark.parametrize("layout,variant,M,N,K,peers", [
+    ("kn", 32, 2048, 2056, 64, 7), ("nk", 16, 2048, 2048, 72, 7), ("nk", 16, 264, 136, 64, 2), ("kn", 40, 1000, 1032, 64, 7),
+    ("nk", 10, 520, 264, 128, 3), ("kn", 35, 1024, 1024, 64, 7), ("nk", 14, 264, 136, 72, 1), ("kn", 41, 264, 200, 72, 7),
+    ("nk", 11, 1024, 1024, 64, 7), ("kn", 42, 200, 264, 136, 2), ("nk", 12, 1024, 1024, 128, 7), ("nk", 13, 64, 16384, 128, 7),
+    ("kn", 43, 72, 136, 64, 7), ("nk", 17, 512, 1024, 136, 7), ("kn", 44, 512, 512, 200, 7), ("nk", 18, 72, 136, 64, 0),
+    ("kn", 38, 512, 1024, 64, 7), ("nk", 25, 512, 1024, 64, 2), ("kn", 39, 512, 1024, 64, 7), ("nk", 9, 512, 1024, 64, 7),
+    ("kn", 36, 72, 136, 64, 2), ("kn", 37, 512, 1024, 64, 7), ("nk", 6, 72, 136, 64, 2), ("nk", 7, 512, 1024, 64, 7),
+    ("kn", 33, 16, 264, 136, 7), ("kn", 33, 16, 4096, 72, 7), ("kn", 33, 16, 28672, 64, 7), ("nk", 21, 8, 4096, 136, 7),
+    ("nk", 34, 16, 4096, 1024, 7)])
+def test_schedules_in_a_row_read_the_fresh_gemm_output(layout, variant, M, N, K, peers):
+    g = torch.Generator(device=DEV).manual_seed(M + N + variant)
+    ints = lambda lo, hi, *shape: torch.randint(lo, hi, shape, generator=g, device=DEV)
+    B = ints(-2, 3, *((K, N) if layout == "kn" else (N, K))).to(torch.bfloat16)
+    bufs = ints(-4, 5, peers, M * N).float()
+    A = torch.empty((M, K), device=DEV, dtype=torch.bfloat16)
+    C = torch.full((3, M, N), float("nan"), device=DEV, dtype=torch.bfloat16)
+    out = torch.full((M * N,), float("nan"), device=DEV)
+    ws = torch.zeros(occ.occ_overlap_workspace_bytes(3), dtype=torch.uint8, device=DEV)
+    err = torch.zeros(1, dtype=torch.int32, device=DEV)
+    comm = torch.cuda.Stream()
+    for n in (1, 1, 3, 1):
+        A.copy_(ints(-2, 3, M, K))
+        # integer sums below 2^24: exact in fp32, rounded to bf16 once
+        ref = (A.float() @ (B.float() if layout == "kn" else B.float().t())).to(torch.bfloat16)
+        want = ref.float().reshape(-1) + bufs.sum(0)
+        torch.cuda.synchronize()
+        occ.occ_overlap_enqueue(A, B, C[:n], workspace=ws, comm_stream=comm, err=err, bufs=bufs, out=out, n_iter=n,
+                                gemm_variant=variant, b_layout=layout, reduce_own=True)
+        torch.cuda.synchronize()
+        assert int(err.item()) == 0
+        for i in range(n):
+            assert torch.equal(C[i].view(torch.int16), ref.view(torch.int16)), (n, i)
+        assert torch.equal(out, want), n
