@@ -57,9 +57,8 @@ typedef enum occ_status {
  * only a smaller tile leaves room for takes that tile (occ_gemm_plan_query
  * tells) or, on large shapes, is refused.
  * Requirements: M, N, K >= 0; K % 8 == 0 and N % 8 == 0 (16-byte rows);
- * A, B, C 16-byte aligned; C must not overlap A or B; K at most 4 M and N at
- * most 16 M (an operand tile is addressed with 32-bit offsets; larger is
- * OCC_EINVAL).  M == 0 or N == 0 is a no-op; K == 0 writes zeros.  Returns
+ * A, B, C 16-byte aligned; C must not overlap A or B; K and N at most 16 M
+ * (an operand tile is addressed with 32-bit offsets; larger is OCC_EINVAL).  M == 0 or N == 0 is a no-op; K == 0 writes zeros.  Returns
  * OCC_ELDS if S_tile + lds_bytes exceeds the device's per-workgroup LDS
  * limit (never clamps).
  */
@@ -80,7 +79,8 @@ enum {
   /* B stored K x N (occ_gemm) */
   OCC_GEMM_KN_256x256x64_8W_2ST = 32,   /* direct-to-LDS; default for large shapes */
   OCC_GEMM_KN_SKINNY_4W_2ST = 33,       /* M <= 16: units of 32, 64 or 128 columns (by N) over the whole K; default for M <= 16 */
-  OCC_GEMM_KN_128x128x64_4W_3ST = 35,   /* register-pipelined (8 waves); default for mid-size shapes */
+  OCC_GEMM_KN_128x128x64_4W_3ST = 35,   /* register-pipelined, 8 waves (the name, from a 4-wave kernel, is
+                                           kept for callers); default for mid-size shapes */
   OCC_GEMM_KN_OPT1_64x64x32 = 36,       /* Table 1 opt1, one stage */
   OCC_GEMM_KN_OPT2_64x64x64 = 37,       /* Table 1 opt2, one stage */
   OCC_GEMM_KN_128x256x32_4W_2ST = 38,   /* two resident workgroups per CU (48 KiB) */
@@ -99,7 +99,7 @@ enum {
   OCC_GEMM_RP_128x64x64_8W_4ST = 11,    /* as 41 */
   OCC_GEMM_RP_64x64x128_4W_4ST = 12,    /* as 42 */
   OCC_GEMM_RP_64x128x128_8W_3ST = 13,   /* register-pipelined; default for M <= 64 and a B beyond 256 MB */
-  OCC_GEMM_DL_128x128x64_4W_3ST = 14,   /* as 35; default for mid-size shapes */
+  OCC_GEMM_DL_128x128x64_4W_3ST = 14,   /* as 35 (its name too); default for mid-size shapes */
   OCC_GEMM_DLP_256x256x64_8W_2ST = 16,  /* direct-to-LDS; default for large shapes */
   OCC_GEMM_RP_32x64x128_4W_3ST = 17,    /* as 43 */
   OCC_GEMM_RP_32x32x128_2W_4ST = 18,    /* as 44 */
@@ -278,18 +278,19 @@ enum { OCC_B_KN = 0 /* K x N, occ_gemm */, OCC_B_NK = 1 /* N x K, occ_gemm_bt */
  *                      time per iteration on MI355X, so schedules whose
  *                      kernels are that short become bound by it.
  *   OCC_DEP_COUNTER -- a device-side counter: every workgroup of K_g^i adds
- *                      one to a per-iteration counter when it is done (after
- *                      its stores, released at device scope), and every
- *                      workgroup of K_c^i waits until the counter reaches
- *                      K_g^i's workgroup count (then acquires) before it
- *                      reads anything.  No host call besides the two kernel
+ *                      one to a per-iteration counter when it is done (where
+ *                      the collective reads C, after its device-scope stores
+ *                      have completed), and every workgroup of K_c^i waits
+ *                      until the counter reaches K_g^i's workgroup count
+ *                      before it reads anything (C with device-scope loads).  No host call besides the two kernel
  *                      launches.  The collective's last workgroup puts the
  *                      counter back to zero.  The wait is bounded: a
- *                      workgroup that has waited 2 s skips its work and the
+ *                      workgroup that has waited 2 s goes on and the
  *                      schedule fails with OCC_ETIMEOUT.  Needs a GEMM and a
- *                      collective that fit on one CU side by side (one comm
- *                      workgroup per CU at most, registers and LDS of both
- *                      within the CU's), else OCC_EINVAL; n_iter <= 1024;
+ *                      collective that fit on one CU side by side: registers
+ *                      and LDS of every pair of the library's kernels do, and
+ *                      more than one comm workgroup per CU is OCC_EINVAL;
+ *                      n_iter <= 1024;
  *                      not with OCC_RUN_GRAPH (a replayed graph may order
  *                      a collective before its GEMM on one queue, and that
  *                      collective would wait out its bound): OCC_EINVAL.

@@ -24,7 +24,7 @@ OCC_B_KN, OCC_B_NK = 0, 1
 OCC_DEP_EVENT, OCC_DEP_COUNTER = 0, 1
 # kernel variants of occ.h, by the layout of B they read
 KN_VARIANTS = {
-    32: "pp 256x256x64 8w 2st", 33: "skinny M<=16, 128-column units",
+    32: "pp 256x256x64 8w 2st", 33: "skinny M<=16, 32-, 64- or 128-column units",
     35: "rp 128x128x64 8w 3st", 36: "opt1 64x64x32 1st", 37: "opt2 64x64x64 1st",
     38: "dl+pipe 128x256x32 4w 2st 2wg/cu", 39: "dl 64x64x64 4w 2st",
     40: "rp 256x128x64 8w 3st", 41: "rp 128x64x64 8w 4st", 42: "rp 64x64x128 4w 4st",

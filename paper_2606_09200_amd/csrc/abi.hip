@@ -161,8 +161,7 @@ int occ_gemm_bt_plan_query(int M, int N, int K, size_t lds_bytes, int variant, i
 int occ_gemm_info(int *tile_lds_bytes, int *max_lds_per_wg, int *lds_per_cu) {
   if (tile_lds_bytes == nullptr || max_lds_per_wg == nullptr || lds_per_cu == nullptr) return OCC_EINVAL;
   occ_gemm_plan p;
-  // the kernel occ_gemm picks for large shapes (any shape with at least one
-  // 256x256 tile per CU takes it)
+  // the kernel occ_gemm picks for large shapes
   int st = occ_gemm_plan_query(8192, 8192, 8192, 0, OCC_GEMM_KN_256x256x64_8W_2ST, 0, &p);
   if (st != OCC_OK) return st;
   *tile_lds_bytes = p.tile_lds_bytes;

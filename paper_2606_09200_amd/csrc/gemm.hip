@@ -181,7 +181,7 @@ const Variant kVariants[] = {
     make_skinny_ldsb_variant<8, 2, 32>(34, "skinny M<=16, B via LDS in 256-byte row pieces, A in registers, 8 waves, K<=8192, K%1024==0, B N x K"),
     // B stored K x N
     make_pp_variant<PpTile<true>>(32, "pp 256x256x64 8w 2st, B K x N"),
-    make_skinny_kn_variant<4, 2, 128>(33, "skinny M<=16, 128-column units, 4 waves, 2 LDS stages, B K x N"),
+    make_skinny_kn_variant<4, 2, 128>(33, "skinny M<=16, units of up to 128 columns, 4 waves, 2 LDS stages, B K x N"),
     make_rp_variant<R128x128<true>, R128x128<true, true>>(35, "rp 128x128x64 8w 3st, B K x N"),
     make_dl_variant<KN64x64_opt1>(36, "dl 64x64x32 opt1 1st, B K x N"),
     make_dl_variant<KN64x64_opt2>(37, "dl 64x64x64 opt2 1st, B K x N"),

@@ -22,11 +22,11 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   return (uint32_t)to_bf16(lo) | ((uint32_t)to_bf16(hi) << 16);
 }
 
-// Stores of C.  THROUGH / `through` (chosen once per tile, not per store: a branch at
-// each 2-byte store cost 1 us of 14): at device scope, i.e. through the XCD's L2 to memory, so that a
-// store that has completed is visible to the whole device (the hooks'
-// release, see hooks_end).
-// Non-temporal otherwise: C is written once and not read again by the kernel.
+// Stores of C.  THROUGH / `through`: at device scope, i.e. through the XCD's L2 to
+// memory, so that a store that has completed is visible to the whole device (the
+// hooks' release, see hooks_end).  Non-temporal otherwise: C is written once and not
+// read again by the kernel.  2-byte stores choose by template, at most once per tile
+// (a branch at each cost 1 us of 14); the 16-byte ones below by a uniform branch.
 template <bool THROUGH>
 __device__ __forceinline__ void store_c(uint16_t *p, uint16_t v) {
   if constexpr (THROUGH) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

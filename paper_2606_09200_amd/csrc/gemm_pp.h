@@ -13,10 +13,12 @@ namespace {
 // workgroup per CU: two waves per SIMD, one of each half of the workgroup
 // (waves 0-3, waves 4-7).
 //
-// What bounds a 256x256 tile is the delivery of its operands (64 KiB per
-// k-step and CU from the L2 through direct-to-LDS DMA) and the chip's power,
-// not the matrix pipes.  A k-step therefore never drains its DMA, and no wave
-// reads LDS while its SIMD's matrix pipe is idle:
+// What bounded the 256x256 tile was the delivery of its operands (64 KiB per
+// k-step and CU from the L2 through direct-to-LDS DMA): 69 % of the MFMA cycles
+// with all waves loading, meeting and multiplying together.  Two groups of waves
+// that take turns at it, the "ping-pong" schedule known from other GPU GEMMs, keep
+// the pipes busy: a k-step never drains its DMA, and no wave reads LDS while its
+// SIMD's matrix pipe is idle:
 //
 //  * Every k-step has two phases: rows 0-127 of the tile (A0) and rows 128-255
 //    (A1), each against all 256 columns, 32 MFMAs per wave.  A phase is a load
@@ -39,11 +41,13 @@ namespace {
 //    nothing is fetched): the counts stay uniform.
 //
 // 16x16x32 MFMAs: they take about 13 % less energy per flop than 32x32x16 on
-// random operands, and under this kernel the board is at its power limit.  The
+// random operands, and what bounds the kernel now is the board's power: 77-79 % (K x
+// N) and 83-88 % (N x K) of the MFMA cycles at 1.5-1.8 GHz, 1396-1400 W of its cap of
+// 1400 (8192^3, sustained; 0 LDS bank conflicts).  The
 // operands go in swapped (B first), so that a lane holds 4 consecutive columns
 // of one row of C; two permlane16 swaps pair two 16-column blocks into 16-byte
-// stores.  At most 224 VGPRs, so that 64 of a SIMD's 512 stay free for a
-// collective's wave.
+// stores.  At most 224 VGPRs (a CPU test reads the built kernels'), so that 64 of a
+// SIMD's 512 stay free for a collective's wave.
 //
 // Measured (MI355X, N(0,1) operands; before = one DMA drain and one barrier per
 // k-step for all waves, 32x32x16): 8192^3 B K x N 0.825 -> 0.725 ms (1.52

@@ -25,7 +25,7 @@ def _case(M, N, K, n_iter, kind, seed):
         outk = "out"
     elif kind == "reduce":
         C = torch.full((M, N), float("nan"), device=DEV, dtype=torch.bfloat16)
-        length = M * N * 3 + 5                     # ragged: a scalar tail kernel too
+        length = M * N * 3 + 5                     # ragged: elements after the last whole position
         comm = dict(bufs=inputs.reduce_chunks(4, length, seed=seed + 1, device=DEV),
                     out=torch.full((length,), float("nan"), device=DEV))
         outk = "out"
