@@ -100,9 +100,7 @@ __global__ __launch_bounds__(kReduceThreads) void reduce_vec_kernel(ChunkPtrs cp
   Pacer pc = pace_start(pace);
   const I n = (I)nvec;
   const I stride = (I)gridDim.x * kReduceThreads;
-  // the loops below run on the wave's first position, so that the pacing is uniform
-  const I lane = (I)(threadIdx.x & 63);
-  I i0 = (I)blockIdx.x * kReduceThreads + (I)__builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
+  I i = (I)blockIdx.x * kReduceThreads + threadIdx.x;
   auto ld = [&](int c, I k) {
     return __builtin_nontemporal_load(
         reinterpret_cast<const f32x4_a4 *>(reinterpret_cast<const char *>(cp.p[c]) + k * (I)sizeof(f32x4)));
@@ -137,7 +135,7 @@ __global__ __launch_bounds__(kReduceThreads) void reduce_vec_kernel(ChunkPtrs cp
   constexpr int C0 = OWN ? 0 : 1;  // first fp32 chunk added to the first term
 
   if constexpr (NC >= 0) {
-    auto trip = [&](auto positions, I i) {
+    auto trip = [&](auto positions) {
       constexpr int U = decltype(positions)::value;
       f32x4 v[NC > 0 ? NC : 1][U], o[U];
       if constexpr (OWN) {
@@ -156,46 +154,43 @@ __global__ __launch_bounds__(kReduceThreads) void reduce_vec_kernel(ChunkPtrs cp
         st(acc, i + u * stride);
       }
     };
-    if constexpr (UNROLL > 1)
-      for (; i0 + 63 + (UNROLL - 1) * stride < n; i0 += UNROLL * stride) {
-        pace_trip(pc);
-        trip(std::integral_constant<int, UNROLL>{}, i0 + lane);
-      }
-    for (; i0 < n; i0 += stride) {
-      pace_trip(pc, 1, UNROLL);
-      if (i0 + lane < n) trip(std::integral_constant<int, 1>{}, i0 + lane);
+    for (bool first = true; i + (UNROLL - 1) * stride < n; i += UNROLL * stride, first = false) {
+      if (!first) pace_wait(pc);
+      trip(std::integral_constant<int, UNROLL>{});
     }
+    if constexpr (UNROLL > 1)
+      for (; i < n; i += stride) trip(std::integral_constant<int, 1>{});
   } else {
     // chunk count known at run time: batches of 8 loads, folded in order
-    for (; i0 < n; i0 += stride) {
-      pace_trip(pc);
-      const I i = i0 + lane;
-      if (i < n) {
-        f32x4 acc = OWN ? ld_own(i) : ld(0, i);
-        for (int c0 = C0; c0 < nchunks; c0 += 8) {
-          f32x4 v[8];
+    for (bool first = true; i < n; i += stride, first = false) {
+      if (!first) pace_wait(pc);
+      f32x4 acc = OWN ? ld_own(i) : ld(0, i);
+      for (int c0 = C0; c0 < nchunks; c0 += 8) {
+        f32x4 v[8];
 #pragma unroll
-          for (int c = 0; c < 8; ++c)
-            if (c0 + c < nchunks) v[c] = ld(c0 + c, i);
+        for (int c = 0; c < 8; ++c)
+          if (c0 + c < nchunks) v[c] = ld(c0 + c, i);
 #pragma unroll
-          for (int c = 0; c < 8; ++c)
-            if (c0 + c < nchunks) acc = add(acc, v[c]);
-        }
-        st(acc, i);
+        for (int c = 0; c < 8; ++c)
+          if (c0 + c < nchunks) acc = add(acc, v[c]);
       }
+      st(acc, i);
     }
   }
-  if (blockIdx.x == gridDim.x - 1 && head + tail > 0) {
-    pace_trip(pc, 1, UNROLL);
-    if ((int)threadIdx.x < head + tail) {
-      const ptrdiff_t j = (int)threadIdx.x < head ? (ptrdiff_t)threadIdx.x - head
-                                                  : (ptrdiff_t)(nvec * 4) + (ptrdiff_t)threadIdx.x - head;
-      float acc = OWN ? widen_own(own + j) : cp.p[0][j];
-      for (int c = C0; c < nchunks; ++c) acc = acc + cp.p[c][j];
-      out[j] = acc;
-    }
+  if (blockIdx.x == gridDim.x - 1 && (int)threadIdx.x < head + tail) {
+    const ptrdiff_t j = (int)threadIdx.x < head ? (ptrdiff_t)threadIdx.x - head
+                                                : (ptrdiff_t)(nvec * 4) + (ptrdiff_t)threadIdx.x - head;
+    float acc = OWN ? widen_own(own + j) : cp.p[0][j];
+    for (int c = C0; c < nchunks; ++c) acc = acc + cp.p[c][j];
+    out[j] = acc;
   }
-  pace_end(pc);
+  if (pace != 0) {
+    // the positions of this workgroup's first lane, and one for the elements above
+    const size_t first = (size_t)blockIdx.x * kReduceThreads, step = (size_t)gridDim.x * kReduceThreads;
+    const size_t positions = (first < nvec ? (nvec - first + step - 1) / step : 0) +
+                             (blockIdx.x == gridDim.x - 1 && head + tail > 0 ? 1 : 0);
+    pace_until(pc.start + pace_share(pace, positions, UNROLL));
+  }
   hooks_end(tr, t0);
 }
 
@@ -224,8 +219,9 @@ __global__ __launch_bounds__(kPermuteThreads) void permute_vec_kernel(const char
   typedef typename std::conditional<ALIGNED, u32x4, u32x4_a1>::type Unit;
   set_wave_priority(prio);
   const HookStart t0 = hooks_begin(tr);
-  Pacer pc = pace_start(pace);
-  constexpr uint32_t ROUND = UNROLL * kPermuteThreads;  // units of a full round: one pacing period
+  // Pacing: a full round of a part waits for the one before it, and the next part (or
+  // the kernel's end) for the time of all bytes of this one, partial round included.
+  uint64_t part_end = 0;
   const int nwork = nchunks * parts;
   for (int w = blockIdx.x; w < nwork; w += gridDim.x) {
     const int chunk = w / parts;
@@ -233,38 +229,38 @@ __global__ __launch_bounds__(kPermuteThreads) void permute_vec_kernel(const char
     const char *s = src + (size_t)pt.p[chunk] * chunk_bytes;
     char *d = dst + (size_t)chunk * chunk_bytes;
     size_t cvec = chunk_bytes / 16;
+    uint32_t edge_units = 0;  // the bytes outside the units, for the pacing
     if constexpr (!ALIGNED) {
       size_t head = (16 - (reinterpret_cast<uintptr_t>(d) & 15)) & 15;
       if (head > chunk_bytes) head = chunk_bytes;
       cvec = (chunk_bytes - head) / 16;
       const size_t edge = chunk_bytes - cvec * 16;  // bytes outside the units
-      if (part == parts - 1 && edge > 0) {
-        pace_trip(pc, 2, ROUND);
-        if (threadIdx.x < edge) {
-          const size_t b = threadIdx.x < head ? threadIdx.x : cvec * 16 + threadIdx.x;
-          d[b] = s[b];
-        }
+      if (part == parts - 1 && threadIdx.x < edge) {
+        const size_t b = threadIdx.x < head ? threadIdx.x : cvec * 16 + threadIdx.x;
+        d[b] = s[b];
       }
+      if (part == parts - 1) edge_units = (uint32_t)(edge + 15) / 16;
       s += head;
       d += head;
     }
     const I lo = (I)(cvec * part / parts);
     const I hi = (I)(cvec * (part + 1) / parts);
+    Pacer pc = pace_start(pace, part_end);
+    if (pace != 0) part_end = pc.start + pace_share(pace, (uint64_t)(hi - lo) + edge_units, UNROLL * kPermuteThreads);
+    bool first = true;
     auto ld = [&](I k) { return __builtin_nontemporal_load(reinterpret_cast<const Unit *>(s + k * (I)16)); };
     auto st = [&](u32x4 v, I k) { __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(d + k * (I)16)); };
+    I i = lo + threadIdx.x;
     u32x4 v[UNROLL];
-    I base = lo;
-    for (; base + ROUND <= hi; base += ROUND) {
-      pace_trip(pc);
-      const I i = base + threadIdx.x;
+    for (; i + (UNROLL - 1) * kPermuteThreads < hi; i += UNROLL * kPermuteThreads) {
+      if (!first) pace_wait(pc);
+      first = false;
 #pragma unroll
       for (int u = 0; u < UNROLL; ++u) v[u] = ld(i + u * kPermuteThreads);
 #pragma unroll
       for (int u = 0; u < UNROLL; ++u) st(v[u], i + u * kPermuteThreads);
     }
-    if (base < hi) {
-      pace_trip(pc, (uint32_t)(hi - base), ROUND);
-      const I i = base + threadIdx.x;
+    if (i < hi) {
 #pragma unroll
       for (int u = 0; u < UNROLL; ++u)
         if (i + u * kPermuteThreads < hi) v[u] = ld(i + u * kPermuteThreads);
@@ -273,7 +269,7 @@ __global__ __launch_bounds__(kPermuteThreads) void permute_vec_kernel(const char
         if (i + u * kPermuteThreads < hi) st(v[u], i + u * kPermuteThreads);
     }
   }
-  pace_end(pc);
+  if (pace != 0) pace_until(part_end);
   hooks_end(tr, t0);
 }
 

@@ -149,38 +149,41 @@ __device__ __forceinline__ void hooks_end(const KHooks &t, const HookStart &s) {
   if (t.signal != nullptr) __hip_atomic_fetch_add(t.signal, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Bandwidth pacing of a streaming loop: a trip that may take `ticks` starts no
-// earlier than the end of the time the trip before it may take, and the loop's
-// end waits for the time of its last one, so a wave's whole transfer takes at
-// least the sum of its trips' ticks however few or short they are (a wave that
-// falls behind does not burst to catch up).  period = 0 disables it.  Call both
-// in wave-uniform control flow: the state then stays in scalar registers.  The
-// wait is a scalar loop on the monotonic constant-rate clock, so it always ends.
+// Bandwidth pacing of a streaming loop: with a period of P ticks, trip j of a
+// wave starts no earlier than P ticks after trip j-1 started (a wave that
+// falls behind does not burst to catch up), and the loop's end waits until
+// `start` plus the time of everything the wave moved, so that a short transfer
+// (one trip, or less than one) keeps the rate too.  P = 0 disables it.  The wait
+// is a scalar loop on the monotonic constant-rate clock, so it always ends.
 struct Pacer {
   uint64_t next;
+  uint64_t start;
   uint32_t period;
 };
 
-__device__ __forceinline__ Pacer pace_start(uint32_t period) { return Pacer{0ull, period}; }
-
-__device__ __forceinline__ uint64_t pace_until(const Pacer &p) {
+__device__ __forceinline__ uint64_t pace_until(uint64_t until) {
   uint64_t t = now_ticks();
-  while (t < p.next) {
+  while (t < until) {
     __builtin_amdgcn_s_sleep(2);
     t = now_ticks();
   }
   return t;
 }
 
-// Before a trip of units / per_period of a period.
-__device__ __forceinline__ void pace_trip(Pacer &p, uint32_t units = 1, uint32_t per_period = 1) {
-  if (p.period == 0) return;
-  p.next = pace_until(p) + ((uint64_t)p.period * units + (per_period - 1)) / per_period;
+// A pacer whose first trip starts at `from` or later.
+__device__ __forceinline__ Pacer pace_start(uint32_t period, uint64_t from = 0) {
+  const uint64_t t = period ? pace_until(from) : 0ull;
+  return Pacer{t + period, t, period};
 }
 
-// After the last trip.
-__device__ __forceinline__ void pace_end(const Pacer &p) {
-  if (p.period != 0) pace_until(p);
+__device__ __forceinline__ void pace_wait(Pacer &p) {
+  if (p.period == 0) return;
+  p.next = pace_until(p.next) + p.period;
+}
+
+// Ticks of n units of which `per_period` take a period, rounded up.
+__device__ __forceinline__ uint64_t pace_share(uint32_t period, uint64_t n, uint32_t per_period) {
+  return (period * n + (per_period - 1)) / per_period;
 }
 
 // Wave issue priority (s_setprio takes an immediate).
